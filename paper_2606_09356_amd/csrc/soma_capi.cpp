@@ -55,7 +55,7 @@ struct Layout {
     size_t mirror_part = 0, halo = 0, acc_tile = 0;
     size_t systems, tiles, chain_id, chain_id2, P[3], C[3], Q[3], D[3], keys, hist, bsum, perm, base, delta, flux, chunks,
         omega, accept, status, partials, obs_out, staging, chain_class, chain_class2, conv, tgt, place_W, place_bsum,
-        ptiles, total;   // base: counts, delta: density delta; ptiles: block tiles
+        ptiles, tile_first, total;   // base: counts, delta: density delta; ptiles: block tiles
     int64_t total_slots = 0, total_cells = 0, total_chains = 0, count_words = 0, total_beads = 0;
     int n_tiles = 0;
     int n_ptiles_cap = 0;   // entries of the block/stream tile table
@@ -86,7 +86,6 @@ inline int64_t align64(int64_t v) { return (v + 63) & ~int64_t(63); }
 struct soma_ctx {
     soma_options opt{};
     std::vector<HostSys> sys;
-    std::vector<Tile> tiles;
     Layout L;
     char *ws = nullptr;
     hipStream_t stream = nullptr;
@@ -95,7 +94,7 @@ struct soma_ctx {
     int waves_per_cu = 0, n_cus = 0;
     int packed = 0;                    // sweep launched over block tiles
     int n_ptiles = 0;
-    std::vector<Tile> ptiles_host;     // the block or stream tiles on the device
+    std::vector<int32_t> tile_first;   // first tile of every system, of the table made last
     int ptiles_packed = 0, ptiles_wpb = 0;   // the tiling and waves per block they were built for
     int device = 0;                    // the GPU the context was created on
     double *scratch_dev = nullptr;     // that GPU's static scratch (soma_observables_noalloc)
@@ -368,6 +367,7 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     // block tiles never outnumber wave tiles; stream tiles may, by a few
     L.ptiles = take(sizeof(Tile) * (size_t)std::max<int64_t>(tiles, stiles));
     L.n_ptiles_cap = (int)std::max<int64_t>(tiles, stiles);
+    L.tile_first = take(sizeof(int32_t) * ((size_t)n_sys + 1));
     L.chain_id = take(sizeof(uint32_t) * chains);
     L.chain_id2 = take(sizeof(uint32_t) * chains);
     for (int a = 0; a < 3; ++a) L.P[a] = take(sizeof(float) * slots);
@@ -461,43 +461,55 @@ void set_shape(soma_ctx *c, int waves_per_block, int waves_per_cu, int xcd_remap
         c->packed = packed && waves_per_cu == 0 && !c->any_zones ? 1 : 0;
 }
 
-// Block tiles for the current waves per block: floor(64 W / P) whole chains
-// of one system per tile.  Stream tiles: the lanes of a system (P per chain)
-// in runs of 62 owned lanes per wave; a tile names its system (low 24 bits),
-// the pair index of its first owned lane within that lane's chain (high 8
-// bits) and that chain.  Uploaded before the next sweep launch.
+// Write the tile table of one kind (0 wave tiles, 1 block tiles of `lanes`
+// lanes, 2 stream tiles) on the device, from the first tile of every system.
+int make_tiles(soma_ctx *c, int kind, int lanes, int cap, Tile *dst, int *n_out)
+{
+    // (kept for the asynchronous copy; the copy of the table before may still
+    // be in flight, but not in soma_create, which makes the first one)
+    std::vector<int32_t> &first = c->tile_first;
+    if (!first.empty()) HIPCHK(c, hipStreamSynchronize(c->stream));
+    first.clear();
+    first.reserve(c->sys.size() + 1);
+    int64_t n = 0;
+    for (const HostSys &h : c->sys) {
+        first.push_back((int32_t)n);
+        const int64_t P = h.dev.P, ch = h.d.n_chains;
+        const int64_t G = kind == 1 ? lanes / P : h.dev.G;
+        n += kind == 2 ? (ch * P + soma::kStreamLanes - 1) / soma::kStreamLanes : (ch + G - 1) / G;
+        if (n > cap) return fail(c, SOMA_EDEVICE, "tile table overflow");
+    }
+    first.push_back((int32_t)n);
+    int32_t *d_first = reinterpret_cast<int32_t *>(c->ws + c->L.tile_first);
+    HIPCHK(c, hipMemcpyAsync(d_first, first.data(), sizeof(int32_t) * first.size(), hipMemcpyHostToDevice, c->stream));
+    soma::MakeTilesArgs a{};
+    a.systems = c->d_sys();
+    a.first = d_first;
+    a.n_sys = (int)c->sys.size();
+    a.n_tiles = (int)n;
+    a.kind = kind;
+    a.lanes = lanes;
+    a.tiles = dst;
+    HIPCHK(c, soma::launch_make_tiles(a, c->stream));
+    *n_out = (int)n;
+    return SOMA_OK;
+}
+
+// The block or stream tiles of the current shape, before the next sweep launch.
 int upload_block_tiles(soma_ctx *c)
 {
     if (!c->packed) return SOMA_OK;
-    // the table depends on the systems (fixed) and the tiling only: this
-    // runs before every batch, and rebuilding a million-entry table costs
-    // milliseconds of host time in front of the launch
+    // the table depends on the systems (fixed) and the tiling only, and this
+    // runs before every batch
     if (c->n_ptiles > 0 && c->ptiles_packed == c->packed &&
         (c->packed == 2 || c->ptiles_wpb == c->waves_per_block))
         return SOMA_OK;
-    std::vector<Tile> t;
-    if (c->packed == 2) {
-        if (c->sys.size() >= (size_t(1) << 24)) return fail(c, SOMA_EINVAL, "stream tiles hold at most 2^24 systems");
-        for (size_t k = 0; k < c->sys.size(); ++k) {
-            const int64_t P = c->sys[k].dev.P, lanes = (int64_t)c->sys[k].d.n_chains * P;
-            for (int64_t l = 0; l < lanes; l += soma::kStreamLanes)
-                t.push_back(Tile{(uint32_t)k | ((uint32_t)(l % P) << 24), (uint32_t)(l / P)});
-        }
-    } else {
-        const int lanes = 64 * c->waves_per_block;
-        for (size_t k = 0; k < c->sys.size(); ++k) {
-            const int Gw = lanes / c->sys[k].dev.P;
-            for (int ch = 0; ch < c->sys[k].d.n_chains; ch += Gw) t.push_back(Tile{(uint32_t)k, (uint32_t)ch});
-        }
-    }
-    if ((int64_t)t.size() > c->L.n_ptiles_cap) return fail(c, SOMA_EDEVICE, "block tile table overflow");
-    HIPCHK(c, hipStreamSynchronize(c->stream));     // the previous table may still be in flight
-    c->ptiles_host = std::move(t);
-    c->n_ptiles = (int)c->ptiles_host.size();
+    if (c->packed == 2 && c->sys.size() >= (size_t(1) << 24))
+        return fail(c, SOMA_EINVAL, "stream tiles hold at most 2^24 systems");
+    int rc = make_tiles(c, c->packed, 64 * c->waves_per_block, c->L.n_ptiles_cap, c->d_ptiles(), &c->n_ptiles);
+    if (rc != SOMA_OK) return rc;
     c->ptiles_packed = c->packed;
     c->ptiles_wpb = c->waves_per_block;
-    HIPCHK(c, hipMemcpyAsync(c->d_ptiles(), c->ptiles_host.data(), sizeof(Tile) * c->ptiles_host.size(),
-                             hipMemcpyHostToDevice, c->stream));
     return SOMA_OK;
 }
 
@@ -593,7 +605,7 @@ int fold_acc(soma_ctx *c)
     if (c->acc_kind < 0) return SOMA_OK;
     const bool stream = c->acc_kind == 2;
     HIPCHK(c, soma::launch_acc_fold(stream ? c->d_ptiles() : c->d_tiles(), stream ? c->n_ptiles : c->L.n_tiles,
-                                    stream, c->acc_tile(), c->accept(), c->stream));
+                                    c->acc_tile(), c->accept(), c->stream));
     c->acc_kind = -1;
     return SOMA_OK;
 }
@@ -620,7 +632,6 @@ int refresh_halo(soma_ctx *c)
 {
     if (c->packed != 2 || c->halo_sweep == c->sweep) return SOMA_OK;
     soma::HaloArgs h{};
-    h.systems = c->d_sys();
     h.ptiles = c->d_ptiles();
     h.n_ptiles = c->n_ptiles;
     for (int d = 0; d < 3; ++d) {
@@ -749,8 +760,8 @@ soma::InitArgs init_args(const soma_ctx *c, const HostSys &h)
     return ia;
 }
 
-// Field coefficients of a system: omega_A = cAA nA + cAB nB + c0 and
-// omega_B = cBA nA + cBB nB + c0 (the umbrella's lambda phi_t / N included;
+// Field coefficients of a system: omega_A = c_same nA + c_other nB + c0
+// and omega_B = c_other nA + c_same nB + c0 (the umbrella's lambda phi_t / N included;
 // its -lambda target_t / N is added per cell by the kernels).
 void set_field_coefs(HostSys &h)
 {
@@ -767,10 +778,8 @@ void set_field_coefs(HostSys &h)
         ab = s * (d.kappaN + d.chiN) * inv_n;
     }
     const double lam = v.umb ? h.umb_lambda : 0.0;
-    v.cAA = (float)(aa + s * lam * inv_n);
-    v.cBB = v.cAA;
-    v.cAB = (float)ab;
-    v.cBA = v.cAB;
+    v.c_same = (float)(aa + s * lam * inv_n);
+    v.c_other = (float)ab;
     v.c0 = (float)(-d.kappaN * inv_n);
     v.umb_coef = (float)(lam * inv_n);
 }
@@ -1166,19 +1175,15 @@ int soma_create(const soma_system_desc *sys, int32_t n_sys, const soma_options *
     }
     set_shape(c, c->waves_per_block, opt->waves_per_cu, opt->launch_order == 0 ? 1 : 0, opt->packed_tiles);
     c->ws = static_cast<char *>(workspace);
-    for (size_t k = 0; k < c->sys.size(); ++k) {
-        const HostSys &h = c->sys[k];
-        for (int t = h.tile_begin; t < h.tile_end; ++t)
-            c->tiles.push_back(Tile{(uint32_t)k, (uint32_t)((t - h.tile_begin) * h.dev.G)});
-    }
     auto bail = [&](int code) { g_create_error = c->err; soma_destroy(c); return code; };
     std::vector<DevSys> dv;
     for (const HostSys &h : c->sys) dv.push_back(h.dev);
     hipError_t e;
     if ((e = hipMemcpyAsync(c->d_sys(), dv.data(), sizeof(DevSys) * dv.size(), hipMemcpyHostToDevice, c->stream)) != hipSuccess)
         return bail(hip_fail(c, e, "upload systems"));
-    if ((e = hipMemcpyAsync(c->d_tiles(), c->tiles.data(), sizeof(Tile) * c->tiles.size(), hipMemcpyHostToDevice, c->stream)) != hipSuccess)
-        return bail(hip_fail(c, e, "upload tiles"));
+    int n_tiles = 0;
+    if ((rc = make_tiles(c, 0, 64, c->L.n_tiles, c->d_tiles(), &n_tiles)) != SOMA_OK) return bail(rc);
+    if (n_tiles != c->L.n_tiles) return bail(fail(c, SOMA_EDEVICE, "tile table size"));
     std::vector<soma::FoldChunk> chunks;
     for (size_t k = 0; k < c->sys.size(); ++k)
         for (int64_t f = 0; f < c->sys[k].dev.n_cells; f += soma::kFoldChunk)

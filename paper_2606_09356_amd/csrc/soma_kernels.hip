@@ -9,7 +9,7 @@
 //   * One wavefront owns a tile of whole chains: lane p of a chain holds the
 //     bead pair (2p, 2p+1), so a chain of N <= 128 beads fits one wave and
 //     the bond neighbours of a bead sit in the same lane or the adjacent
-//     lane (cross-lane exchange with ds_bpermute; no barrier).
+//     lane (a whole-wave DPP shift; no barrier).
 //   * Positions are SoA with chains stored at an even stride, so each lane
 //     reads and writes one 8-byte pair per coordinate: fully coalesced.
 //   * The even pass moves bead 2p of every lane, the odd pass bead 2p+1;
@@ -89,12 +89,11 @@ __device__ __forceinline__ Draw move_draw(uint32_t bead, uint32_t chain, uint32_
     return d;
 }
 
-// Periodic wrap of an unwrapped cell index into [0, n); exact for |i| < 2^23
-// (24-bit multiply: |q| < 2^23, n < 2^15).
+// Periodic wrap of an unwrapped cell index into [0, n); exact for |i| <= 2^23.
 __device__ __forceinline__ int wrap_cell(int i, int n, float inv_n)
 {
     const int q = (int)floorf((float)i * inv_n);
-    int r = i - __mul24(q, n);
+    int r = i - q * n;
     r = r < 0 ? r + n : r;
     r = r >= n ? r - n : r;
     return r;
@@ -110,32 +109,70 @@ __device__ __forceinline__ int wrap_step(int i, int n)
     return (int)min(min(u, u + m), u - m);
 }
 
-__device__ __forceinline__ bool wrapped(int w, int n) { return (uint32_t)w < (uint32_t)n; }
-
 // ---------------------------------------------------------------------------
 // Position representations
 // ---------------------------------------------------------------------------
+// The system table, the tile tables, the sweep counter and the kernel's own
+// arguments are not written while a kernel runs: read through the constant
+// address space, a wave-uniform address is a scalar load wherever it stands,
+// also behind stores and in divergent code.
+#define SOMA_CONST __attribute__((address_space(4)))
+using SysPtr = const SOMA_CONST DevSys *;
+using TilePtr = const SOMA_CONST Tile *;
+using ArgPtr = const SOMA_CONST SweepArgs *;
+
+__device__ __forceinline__ SysPtr sys_at(const DevSys *table, uint32_t k) { return (SysPtr)(uintptr_t)table + k; }
+__device__ __forceinline__ Tile tile_at(const Tile *table, int k)
+{
+    const TilePtr t = (TilePtr)(uintptr_t)table + k;
+    return Tile{t->sys, t->chain0, t->slot, t->chain, t->lanes, t->inv_P};
+}
+
+// The same pointer as a new value: what is read through it cannot be read
+// earlier.  The sweep kernels take the arguments and system scalars of each
+// of their phases through such a pointer, so that they do not hold all of
+// them in SGPRs from the start (eight waves per SIMD leave a wave 72 SGPRs;
+// what does not fit costs a v_writelane and v_readlanes per value: 288 of
+// the 1127 vector instructions of the cell + offset stream kernel before).
+template <class T>
+__device__ __forceinline__ T later(T p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Element at a byte offset from a wave-uniform base in device memory (one
+// 32-bit register of address per lane).
+#define SOMA_GLOBAL __attribute__((address_space(1)))
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef int i2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+template <class T>
+__device__ __forceinline__ T ld_off(const void *base, uint32_t off)
+{
+    return *(const SOMA_GLOBAL T *)((const SOMA_GLOBAL char *)base + off);
+}
+template <class T>
+__device__ __forceinline__ void st_off(void *base, uint32_t off, T v)
+{
+    *(SOMA_GLOBAL T *)((SOMA_GLOBAL char *)base + off) = v;
+}
+
+// Two 32-bit words as one 64-bit value (built as a vector, the first word's
+// load is widened to two words and keeps its struct in memory).
+template <class T>
+__device__ __forceinline__ uint64_t pair_bits(T a, T b)
+{
+    return (uint64_t)__builtin_bit_cast(uint32_t, a) | (uint64_t)__builtin_bit_cast(uint32_t, b) << 32;
+}
+
 struct SysView {            // the per-system scalars a wave needs (SGPR resident)
     int n0, n1, n2;
-    float inv_n0, inv_n1, inv_n2;
     float e0, e1, e2;
     float ie0, ie1, ie2;
     bool dyadic;            // every edge a power of two: x * (1/edge) is the exact quotient
 };
-
-// floor(x / e) of the exact quotient for the FP32 cell edge e.  The product
-// with the rounded reciprocal can be one off next to a face when e is not a
-// power of two; the sign of x - k e, exact after one FMA rounding, corrects
-// it (|x / e| < 2^22, so the product is within one of the quotient).
-__device__ __forceinline__ float floor_div(float x, float e, float ie, bool dyadic)
-{
-    float k = floorf(x * ie);
-    if (!dyadic) {
-        if (fmaf(-k, e, x) < 0.0f) k -= 1.0f;
-        else if (fmaf(-(k + 1.0f), e, x) >= 0.0f) k += 1.0f;
-    }
-    return k;
-}
 
 struct BeadF32 {
     float x, y, z;
@@ -202,90 +239,91 @@ __device__ __forceinline__ BeadCell propose(const BeadCell &a, const Draw &d, co
     return n;
 }
 
-// NGP cell of a bead: wrapped cell coordinates and, for FP32 positions, the
-// unwrapped floors (to step to the cell of a trial position; for cell +
-// offset positions fz alone, the unwrapped z index).  `bad` is set
-// when the unwrapped index leaves the range the wrap handles (or the
-// coordinate is not finite); the bead is then counted in cell 0.
+// NGP cell of a bead: wrapped cell coordinates and the unwrapped z index
+// (for walls and zones).
 struct CellPos {
-    int x, y, z;
-    float fx, fy, fz;
+    int x, y, z, uz;
 };
 
-// Beads almost always lie within one image of the box, where wrap_step is
-// the wrap; the general form (and the range check) runs only for the lanes
-// that need it.
-__device__ __forceinline__ CellPos locate(const BeadF32 &a, const SysView &v, bool &bad)
+// Unwrapped NGP indexes of M beads: floor of the exact quotient x / e for the
+// FP32 cell edge e.  The product with the rounded reciprocal can be one off
+// next to a face when e is not a power of two (|x / e| < 2^22, so never more
+// than one).  r = x - k e corrects it: one FMA, whose rounding keeps the sign
+// and, for r < 2 e (a multiple of the smaller ulp), the comparison with e.
+template <int M>
+__device__ __forceinline__ void ngp_index(const BeadF32 (&b)[M], const SysView &v, int (&k)[M][3])
 {
-    CellPos c;
-    c.fx = floor_div(a.x, v.e0, v.ie0, v.dyadic);
-    c.fy = floor_div(a.y, v.e1, v.ie1, v.dyadic);
-    c.fz = floor_div(a.z, v.e2, v.ie2, v.dyadic);
-    const float lim = (float)kCellLimit;
-    c.x = wrap_step((int)c.fx, v.n0);
-    c.y = wrap_step((int)c.fy, v.n1);
-    c.z = wrap_step((int)c.fz, v.n2);
-    // (a non-finite coordinate fails the magnitude test)
-    if (!(wrapped(c.x, v.n0) && wrapped(c.y, v.n1) && wrapped(c.z, v.n2) && fabsf(c.fx) < lim &&
-          fabsf(c.fy) < lim && fabsf(c.fz) < lim)) {
-        if (!(fabsf(c.fx) < lim && fabsf(c.fy) < lim && fabsf(c.fz) < lim)) {
-            bad = true;
-            c.x = c.y = c.z = 0;
-            c.fx = c.fy = c.fz = 0.0f;
-            return c;
-        }
-        c.x = wrap_cell((int)c.fx, v.n0, v.inv_n0);
-        c.y = wrap_cell((int)c.fy, v.n1, v.inv_n1);
-        c.z = wrap_cell((int)c.fz, v.n2, v.inv_n2);
+    float f[M][3];
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        f[j][0] = floorf(b[j].x * v.ie0);
+        f[j][1] = floorf(b[j].y * v.ie1);
+        f[j][2] = floorf(b[j].z * v.ie2);
+        for (int d = 0; d < 3; ++d) k[j][d] = (int)f[j][d];
     }
-    return c;
+    if (!v.dyadic) {
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const float r0 = fmaf(-f[j][0], v.e0, b[j].x), r1 = fmaf(-f[j][1], v.e1, b[j].y),
+                        r2 = fmaf(-f[j][2], v.e2, b[j].z);
+            k[j][0] += (int)(r0 >= v.e0) - (int)(r0 < 0.0f);
+            k[j][1] += (int)(r1 >= v.e1) - (int)(r1 < 0.0f);
+            k[j][2] += (int)(r2 >= v.e2) - (int)(r2 < 0.0f);
+        }
+    }
 }
-// (cell mode: fz carries the unwrapped z index, for walls and zones)
-__device__ __forceinline__ CellPos locate(const BeadCell &a, const SysView &v, bool &bad)
+template <int M>
+__device__ __forceinline__ void ngp_index(const BeadCell (&b)[M], const SysView &v, int (&k)[M][3])
 {
-    const int kx = ngp(a.cx, a.ox, v.e0), ky = ngp(a.cy, a.oy, v.e1), kz = ngp(a.cz, a.oz, v.e2);
-    CellPos c{wrap_step(kx, v.n0), wrap_step(ky, v.n1), wrap_step(kz, v.n2), 0.0f, 0.0f, (float)kz};
-    if (!(wrapped(c.x, v.n0) && wrapped(c.y, v.n1) && wrapped(c.z, v.n2))) {
-        if (kx <= -kCellLimit || kx >= kCellLimit || ky <= -kCellLimit || ky >= kCellLimit ||
-            kz <= -kCellLimit || kz >= kCellLimit) {
-            bad = true;
-            c.x = c.y = c.z = 0;
-            c.fz = 0.0f;
-            return c;
-        }
-        c.x = wrap_cell(kx, v.n0, v.inv_n0);
-        c.y = wrap_cell(ky, v.n1, v.inv_n1);
-        c.z = wrap_cell(kz, v.n2, v.inv_n2);
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        k[j][0] = ngp(b[j].cx, b[j].ox, v.e0);
+        k[j][1] = ngp(b[j].cy, b[j].oy, v.e1);
+        k[j][2] = ngp(b[j].cz, b[j].oz, v.e2);
     }
-    return c;
 }
 
-// Cell of a trial position.  The move half-width is below 0.99 cell edges,
-// so the unwrapped index changes by at most one per axis (clamped so that a
-// non-finite coordinate still yields an in-range cell).
-__device__ __forceinline__ int clamp1(int k) { return max(-1, min(k, 1)); }
-
-__device__ __forceinline__ CellPos step(const CellPos &o, const BeadF32 &, const BeadF32 &n, const SysView &v)
+// Cells of M beads, the first M0 of them stored beads, the others trial
+// positions.  Beads almost always lie within one image of the box, where
+// wrap_step is the wrap; the general form (and the range check) runs only
+// for the lanes that need it.  A bead whose unwrapped index leaves the range
+// that the general wrap handles (or whose coordinate is not finite: the
+// conversion saturates) is counted in cell 0; for a stored bead of a lane
+// with `report` that is flagged in *status.
+template <int M0, class Bead, int M>
+__device__ __forceinline__ void cells_of(const Bead (&b)[M], const SysView &v, SysPtr S, bool report,
+                                         uint32_t *status, CellPos (&c)[M])
 {
-    CellPos c;
-    c.fx = floor_div(n.x, v.e0, v.ie0, v.dyadic);
-    c.fy = floor_div(n.y, v.e1, v.ie1, v.dyadic);
-    c.fz = floor_div(n.z, v.e2, v.ie2, v.dyadic);
-    c.x = wrap_step(o.x + clamp1((int)(c.fx - o.fx)), v.n0);
-    c.y = wrap_step(o.y + clamp1((int)(c.fy - o.fy)), v.n1);
-    c.z = wrap_step(o.z + clamp1((int)(c.fz - o.fz)), v.n2);
-    return c;
-}
-__device__ __forceinline__ CellPos step(const CellPos &o, const BeadCell &ob, const BeadCell &n, const SysView &v)
-{
-    // (a trial move is shorter than one cell edge, so the NGP index changes
-    // by -1, 0 or 1 per axis)
-    const int dz = ngp(n.cz, n.oz, v.e2) - ngp(ob.cz, ob.oz, v.e2);
-    CellPos c{0, 0, 0, 0.0f, 0.0f, o.fz + (float)dz};
-    c.x = wrap_step(o.x + (ngp(n.cx, n.ox, v.e0) - ngp(ob.cx, ob.ox, v.e0)), v.n0);
-    c.y = wrap_step(o.y + (ngp(n.cy, n.oy, v.e1) - ngp(ob.cy, ob.oy, v.e1)), v.n1);
-    c.z = wrap_step(o.z + dz, v.n2);
-    return c;
+    int k[M][3];
+    ngp_index(b, v, k);
+    uint32_t m0 = 0, m1 = 0, m2 = 0;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        c[j] = CellPos{wrap_step(k[j][0], v.n0), wrap_step(k[j][1], v.n1), wrap_step(k[j][2], v.n2), k[j][2]};
+        m0 = max(m0, (uint32_t)c[j].x);
+        m1 = max(m1, (uint32_t)c[j].y);
+        m2 = max(m2, (uint32_t)c[j].z);
+    }
+    if (m0 >= (uint32_t)v.n0 || m1 >= (uint32_t)v.n1 || m2 >= (uint32_t)v.n2) {
+        const SysPtr Q = later(S);
+        const float i0 = Q->inv_n[0], i1 = Q->inv_n[1], i2 = Q->inv_n[2];
+        bool bad = false;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const int lim = j < M0 ? kCellLimit - 1 : kCellLimit;
+            bool in = true;
+            for (int d = 0; d < 3; ++d) in = in && k[j][d] >= -lim && k[j][d] <= lim;
+            if (in) {
+                c[j].x = wrap_cell(k[j][0], v.n0, i0);
+                c[j].y = wrap_cell(k[j][1], v.n1, i1);
+                c[j].z = wrap_cell(k[j][2], v.n2, i2);
+            } else {
+                c[j] = CellPos{0, 0, 0, 0};
+                bad = bad || j < M0;
+            }
+        }
+        if (bad && report) atomicOr(status, ST_CELL_OVERFLOW);
+    }
 }
 
 // Linear index (x * ny + y) * nz + z with 24-bit multiplies (nx * ny <= 2^24).
@@ -294,29 +332,37 @@ __device__ __forceinline__ int lin(const CellPos &c, const SysView &v)
     return (int)__umul24((uint32_t)(__umul24((uint32_t)c.x, (uint32_t)v.n1) + c.y), (uint32_t)v.n2) + c.z;
 }
 
-template <class Bead>
-__device__ __forceinline__ int cell_of(const Bead &a, const SysView &v, bool &bad)
+// Value of the lane before (0 in lane 0) or after (0 in lane 63): a
+// whole-wave DPP shift, one VALU move per word, where a shuffle goes through
+// the LDS unit and its latency twice per tile.
+template <int CTRL, class T>
+__device__ __forceinline__ T wave_shift(T x)
 {
-    return lin(locate(a, v, bad), v);
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppShr1 = 0x138, kDppShl1 = 0x130;
+template <int CTRL>
+__device__ __forceinline__ BeadF32 wave_shift(const BeadF32 &a)
+{
+    return BeadF32{wave_shift<CTRL>(a.x), wave_shift<CTRL>(a.y), wave_shift<CTRL>(a.z)};
+}
+template <int CTRL>
+__device__ __forceinline__ BeadCell wave_shift(const BeadCell &a)
+{
+    return BeadCell{wave_shift<CTRL>(a.cx), wave_shift<CTRL>(a.cy), wave_shift<CTRL>(a.cz),
+                    wave_shift<CTRL>(a.ox), wave_shift<CTRL>(a.oy), wave_shift<CTRL>(a.oz)};
 }
 
-__device__ __forceinline__ BeadF32 shfl_up1(const BeadF32 &a)
+// c ? a : b, component by component and by value (unary plus: a conditional
+// of two lvalues would choose between addresses and keep the beads in memory).
+__device__ __forceinline__ BeadF32 pick(bool c, BeadF32 a, BeadF32 b)
 {
-    return BeadF32{__shfl_up(a.x, 1), __shfl_up(a.y, 1), __shfl_up(a.z, 1)};
+    return BeadF32{c ? +a.x : +b.x, c ? +a.y : +b.y, c ? +a.z : +b.z};
 }
-__device__ __forceinline__ BeadF32 shfl_down1(const BeadF32 &a)
+__device__ __forceinline__ BeadCell pick(bool c, BeadCell a, BeadCell b)
 {
-    return BeadF32{__shfl_down(a.x, 1), __shfl_down(a.y, 1), __shfl_down(a.z, 1)};
-}
-__device__ __forceinline__ BeadCell shfl_up1(const BeadCell &a)
-{
-    return BeadCell{__shfl_up(a.cx, 1), __shfl_up(a.cy, 1), __shfl_up(a.cz, 1),
-                    __shfl_up(a.ox, 1), __shfl_up(a.oy, 1), __shfl_up(a.oz, 1)};
-}
-__device__ __forceinline__ BeadCell shfl_down1(const BeadCell &a)
-{
-    return BeadCell{__shfl_down(a.cx, 1), __shfl_down(a.cy, 1), __shfl_down(a.cz, 1),
-                    __shfl_down(a.ox, 1), __shfl_down(a.oy, 1), __shfl_down(a.oz, 1)};
+    return BeadCell{c ? +a.cx : +b.cx, c ? +a.cy : +b.cy, c ? +a.cz : +b.cz,
+                    c ? +a.ox : +b.ox, c ? +a.oy : +b.oy, c ? +a.oz : +b.oz};
 }
 
 // Bond neighbours of a lane's bead pair: the odd bead of the lane before
@@ -326,7 +372,7 @@ __device__ __forceinline__ BeadCell shfl_down1(const BeadCell &a)
 template <bool BT, class Bead>
 __device__ __forceinline__ Bead left_neighbour(const Bead &b1)
 {
-    Bead l = shfl_up1(b1);
+    Bead l = wave_shift<kDppShr1>(b1);
     if constexpr (BT) {
         __shared__ Bead edge[16];
         const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
@@ -339,7 +385,7 @@ __device__ __forceinline__ Bead left_neighbour(const Bead &b1)
 template <bool BT, class Bead>
 __device__ __forceinline__ Bead right_neighbour(const Bead &b0)
 {
-    Bead r = shfl_down1(b0);
+    Bead r = wave_shift<kDppShl1>(b0);
     if constexpr (BT) {
         __shared__ Bead edge[16];
         const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
@@ -356,73 +402,69 @@ struct PosArrays {
     float *P0, *P1, *P2;
     int *C0, *C1, *C2;
 };
+template <class A>
+__device__ __forceinline__ PosArrays pos_arrays(const A &a) { return PosArrays{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2}; }
+__device__ __forceinline__ PosArrays pos_arrays(ArgPtr a) { return PosArrays{a->P0, a->P1, a->P2, a->C0, a->C1, a->C2}; }
 
+// The pair at byte offset `off` (8 per pair) from slot `first` of each array.
+// Consecutive lanes of a tile hold consecutive pairs, so `first` is uniform.
 // Position lines stay in the caches between a wave's loads and its stores:
 // most stored lines are partial (only changed pairs are written back) and are
 // completed in the L2 from the loaded data before they reach memory.
 // (Non-temporal loads or stores, which keep lines out of the caches, made the
 // sweep slower.)
-__device__ __forceinline__ float2 ld2(const float *p) { return *reinterpret_cast<const float2 *>(p); }
-__device__ __forceinline__ int2 ld2(const int *p) { return *reinterpret_cast<const int2 *>(p); }
-__device__ __forceinline__ void st2(float *p, float x, float y) { *reinterpret_cast<float2 *>(p) = make_float2(x, y); }
-__device__ __forceinline__ void st2(int *p, int x, int y) { *reinterpret_cast<int2 *>(p) = make_int2(x, y); }
-
-__device__ __forceinline__ void load_pair(const PosArrays &A, int64_t slot, BeadF32 &a, BeadF32 &b)
+__device__ __forceinline__ void load_pair(const PosArrays &A, int64_t first, uint32_t off, BeadF32 &a, BeadF32 &b)
 {
-    const float2 x = ld2(A.P0 + slot);
-    const float2 y = ld2(A.P1 + slot);
-    const float2 z = ld2(A.P2 + slot);
+    const f2 x = ld_off<f2>(A.P0 + first, off), y = ld_off<f2>(A.P1 + first, off),
+                 z = ld_off<f2>(A.P2 + first, off);
     a = BeadF32{x.x, y.x, z.x};
     b = BeadF32{x.y, y.y, z.y};
 }
-__device__ __forceinline__ void store_pair(const PosArrays &A, int64_t slot, const BeadF32 &a,
+__device__ __forceinline__ void load_pair(const PosArrays &A, int64_t first, uint32_t off, BeadCell &a, BeadCell &b)
+{
+    const i2 cx = ld_off<i2>(A.C0 + first, off), cy = ld_off<i2>(A.C1 + first, off),
+               cz = ld_off<i2>(A.C2 + first, off);
+    const f2 x = ld_off<f2>(A.P0 + first, off), y = ld_off<f2>(A.P1 + first, off),
+                 z = ld_off<f2>(A.P2 + first, off);
+    a = BeadCell{cx.x, cy.x, cz.x, x.x, y.x, z.x};
+    b = BeadCell{cx.y, cy.y, cz.y, x.y, y.y, z.y};
+}
+__device__ __forceinline__ void store_pair(const PosArrays &A, int64_t first, uint32_t off, const BeadF32 &a,
                                            const BeadF32 &b)
 {
-    st2(A.P0 + slot, a.x, b.x);
-    st2(A.P1 + slot, a.y, b.y);
-    st2(A.P2 + slot, a.z, b.z);
+    st_off(A.P0 + first, off, pair_bits(a.x, b.x));
+    st_off(A.P1 + first, off, pair_bits(a.y, b.y));
+    st_off(A.P2 + first, off, pair_bits(a.z, b.z));
+}
+__device__ __forceinline__ void store_pair(const PosArrays &A, int64_t first, uint32_t off, const BeadCell &a,
+                                           const BeadCell &b)
+{
+    st_off(A.C0 + first, off, pair_bits(a.cx, b.cx));
+    st_off(A.C1 + first, off, pair_bits(a.cy, b.cy));
+    st_off(A.C2 + first, off, pair_bits(a.cz, b.cz));
+    st_off(A.P0 + first, off, pair_bits(a.ox, b.ox));
+    st_off(A.P1 + first, off, pair_bits(a.oy, b.oy));
+    st_off(A.P2 + first, off, pair_bits(a.oz, b.oz));
 }
 // Store what a sweep changed: nothing for a pair whose two moves were
 // rejected; in cell mode, each cell word only when a bead of the pair left
 // its cell along that axis (a few percent of the beads), so most cell
 // sectors are never written back.
-__device__ __forceinline__ void store_moved(const PosArrays &A, int64_t slot, const BeadF32 &a, const BeadF32 &b,
-                                            const BeadF32 &, const BeadF32 &, bool moved)
+__device__ __forceinline__ void store_moved(const PosArrays &A, int64_t first, uint32_t off, const BeadF32 &a,
+                                            const BeadF32 &b, const BeadF32 &, const BeadF32 &, bool moved)
 {
-    if (moved) store_pair(A, slot, a, b);
+    if (moved) store_pair(A, first, off, a, b);
 }
-__device__ __forceinline__ void store_moved(const PosArrays &A, int64_t slot, const BeadCell &a, const BeadCell &b,
-                                            const BeadCell &oa, const BeadCell &ob, bool moved)
+__device__ __forceinline__ void store_moved(const PosArrays &A, int64_t first, uint32_t off, const BeadCell &a,
+                                            const BeadCell &b, const BeadCell &oa, const BeadCell &ob, bool moved)
 {
     if (!moved) return;
-    if (a.cx != oa.cx || b.cx != ob.cx) st2(A.C0 + slot, a.cx, b.cx);
-    if (a.cy != oa.cy || b.cy != ob.cy) st2(A.C1 + slot, a.cy, b.cy);
-    if (a.cz != oa.cz || b.cz != ob.cz) st2(A.C2 + slot, a.cz, b.cz);
-    st2(A.P0 + slot, a.ox, b.ox);
-    st2(A.P1 + slot, a.oy, b.oy);
-    st2(A.P2 + slot, a.oz, b.oz);
-}
-
-__device__ __forceinline__ void load_pair(const PosArrays &A, int64_t slot, BeadCell &a, BeadCell &b)
-{
-    const int2 cx = ld2(A.C0 + slot);
-    const int2 cy = ld2(A.C1 + slot);
-    const int2 cz = ld2(A.C2 + slot);
-    const float2 x = ld2(A.P0 + slot);
-    const float2 y = ld2(A.P1 + slot);
-    const float2 z = ld2(A.P2 + slot);
-    a = BeadCell{cx.x, cy.x, cz.x, x.x, y.x, z.x};
-    b = BeadCell{cx.y, cy.y, cz.y, x.y, y.y, z.y};
-}
-__device__ __forceinline__ void store_pair(const PosArrays &A, int64_t slot, const BeadCell &a,
-                                           const BeadCell &b)
-{
-    st2(A.C0 + slot, a.cx, b.cx);
-    st2(A.C1 + slot, a.cy, b.cy);
-    st2(A.C2 + slot, a.cz, b.cz);
-    st2(A.P0 + slot, a.ox, b.ox);
-    st2(A.P1 + slot, a.oy, b.oy);
-    st2(A.P2 + slot, a.oz, b.oz);
+    if (a.cx != oa.cx || b.cx != ob.cx) st_off(A.C0 + first, off, pair_bits(a.cx, b.cx));
+    if (a.cy != oa.cy || b.cy != ob.cy) st_off(A.C1 + first, off, pair_bits(a.cy, b.cy));
+    if (a.cz != oa.cz || b.cz != ob.cz) st_off(A.C2 + first, off, pair_bits(a.cz, b.cz));
+    st_off(A.P0 + first, off, pair_bits(a.ox, b.ox));
+    st_off(A.P1 + first, off, pair_bits(a.oy, b.oy));
+    st_off(A.P2 + first, off, pair_bits(a.oz, b.oz));
 }
 
 // ---------------------------------------------------------------------------
@@ -448,19 +490,21 @@ struct RawCount {
     uint32_t w0, w1, d0, d1;
 };
 
+// (cnt, dprev: first count word of the wave's system; a context has fewer
+// than 2^30 count words, so a byte offset fits 32 bits)
 template <int CW, bool FI>
-__device__ __forceinline__ RawCount load_raw(const uint32_t *cnt, const uint32_t *dprev, int64_t cell)
+__device__ __forceinline__ RawCount load_raw(const uint32_t *cnt, const uint32_t *dprev, int cell)
 {
     RawCount r{0u, 0u, 0u, 0u};
     if constexpr (CW == COUNT_U16) {
-        r.w0 = cnt[cell];
-        if constexpr (FI) r.d0 = dprev[cell];
+        r.w0 = ld_off<uint32_t>(cnt, (uint32_t)cell << 2);
+        if constexpr (FI) r.d0 = ld_off<uint32_t>(dprev, (uint32_t)cell << 2);
     } else {
-        const uint2 w = *reinterpret_cast<const uint2 *>(cnt + 2 * cell);
+        const u2 w = ld_off<u2>(cnt, (uint32_t)cell << 3);
         r.w0 = w.x;
         r.w1 = w.y;
         if constexpr (FI) {
-            const uint2 d = *reinterpret_cast<const uint2 *>(dprev + 2 * cell);
+            const u2 d = ld_off<u2>(dprev, (uint32_t)cell << 3);
             r.d0 = d.x;
             r.d1 = d.y;
         }
@@ -497,12 +541,17 @@ __device__ __forceinline__ uint2 counts_of(const RawCount &r)
 // update, which runs four loops on lanes that are mostly idle: 8192 beads
 // 7.2 -> 5.4 us a sweep, 17.2M beads FP32 230 -> 193 us, 124.6M beads cell +
 // offset 1.68 -> 1.55 ms.)  A
-// wave makes at most 4 updates per lane with cell words and at most 6 with
-// face fluxes.
-constexpr int kListCells = 4 * kWave;
-constexpr int kListFaces = 6 * kWave;
+// wave makes at most 4 updates per lane with cell words; with face fluxes the
+// beads that moved are packed into a list of records first, and every 64 of
+// them give at most 3 updates each.
+constexpr int kListCells = 4 * kWave;      // 2 words per entry
+constexpr int kListFaces = 3 * kWave;      // the face entries of 64 records,
+constexpr int kFaceRecs = 2 * kWave;       // and the records (4 words each)
 constexpr int kMergeTab = 256;             // bytes of the table (one lane number per slot)
-constexpr int list_words(int cap) { return 2 * cap + kMergeTab / 4; }
+constexpr int list_words(bool faces)
+{
+    return (faces ? 2 * kListFaces + 4 * kFaceRecs : 2 * kListCells) + kMergeTab / 4;
+}
 
 // Multiplicative hash of the low 24 bits of the key.  The product is taken
 // with the full-rate 24-bit multiply.
@@ -524,20 +573,22 @@ __device__ __forceinline__ uint32_t lane_rank(uint64_t m)
 __device__ __forceinline__ uint32_t list_push2(uint32_t *list, uint32_t n, bool on, uint32_t k0, uint32_t v0,
                                                uint32_t k1, uint32_t v1)
 {
-    const uint64_t m = __ballot(on);
+    const uint64_t m = __builtin_amdgcn_ballot_w64(on);
     if (on) *reinterpret_cast<uint4 *>(list + 2 * n + 4 * lane_rank(m)) = make_uint4(k0, v0, k1, v1);
     return n + 2u * (uint32_t)__popcll(m);
 }
 __device__ __forceinline__ uint32_t list_push(uint32_t *list, uint32_t n, bool on, uint32_t k, uint32_t v)
 {
-    const uint64_t m = __ballot(on);
+    const uint64_t m = __builtin_amdgcn_ballot_w64(on);
     if (on) *reinterpret_cast<uint2 *>(list + 2 * (n + lane_rank(m))) = make_uint2(k, v);
     return n + (uint32_t)__popcll(m);
 }
 
 // Merge the n entries of the wave's list and add every nonzero sum to its
-// word of dst (one device atomic each).  LDS operations of one wave execute
+// word of dst (one device atomic each; without WIDE the byte offsets fit 32
+// bits).  LDS operations of one wave execute
 // in order; the fences keep the compiler from reordering them.
+template <bool WIDE>
 __device__ __forceinline__ void list_flush(uint32_t *list, uint8_t *tab, uint32_t n, uint32_t *dst)
 {
     const uint32_t lane = threadIdx.x & 63;
@@ -555,7 +606,8 @@ __device__ __forceinline__ void list_flush(uint32_t *list, uint8_t *tab, uint32_
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             if (!dup) {
                 const uint32_t v = list[2 * i + 1];
-                if (v != 0u) __hip_atomic_fetch_add(dst + e.x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                uint32_t *word = WIDE ? dst + e.x : reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(dst) + (e.x << 2));
+                if (v != 0u) __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }
@@ -563,9 +615,9 @@ __device__ __forceinline__ void list_flush(uint32_t *list, uint8_t *tab, uint32_
 
 // Word index and packed increment of one bead of type t in a cell.
 template <int CW>
-__device__ __forceinline__ uint32_t count_word(int64_t cell, int t)
+__device__ __forceinline__ uint32_t count_word(int cell, int t)
 {
-    return CW == COUNT_U16 ? (uint32_t)cell : (uint32_t)(2 * cell + t);
+    return CW == COUNT_U16 ? (uint32_t)cell : 2u * (uint32_t)cell + (uint32_t)t;
 }
 template <int CW>
 __device__ __forceinline__ uint32_t count_inc(int t)
@@ -604,417 +656,81 @@ __device__ __forceinline__ bool scatter_count(uint32_t *cnt, int64_t cell, int t
     }
 }
 
+// omega_A = same nA + other nB + c0, omega_B = other nA + same nB + c0
 struct FieldCoef {
-    float aa, ab, ba, bb, c0;
+    float same, other, c0;
 };
+__device__ __forceinline__ FieldCoef field_coef(SysPtr S) { return FieldCoef{S->c_same, S->c_other, S->c0}; }
 
 // omega_t of a cell from its counts (affine in the counts).  The same
 // function produces the fields the sweep uses and the ones soma_fields reports.
 __device__ __forceinline__ float omega_of(const FieldCoef &f, uint2 n, int t)
 {
-    const float a = (float)n.x, b = (float)n.y;
-    return t ? fmaf(f.ba, a, fmaf(f.bb, b, f.c0)) : fmaf(f.aa, a, fmaf(f.ab, b, f.c0));
+    const float ca = t ? f.other : f.same, cb = t ? f.same : f.other;
+    return fmaf(ca, (float)n.x, fmaf(cb, (float)n.y, f.c0));
 }
 
-template <int CW>
-__device__ __forceinline__ float omega_at(bool frozen, const float2 *omega, const uint32_t *cnt,
-                                          int64_t cell_off, int cell, int t, const FieldCoef &f)
+// The 32 bead types from bead 32 (i / 32) of a chain of class cls, shifted so
+// that bit 0 is bead i's (pat_a and pat_b are consecutive in the table; one
+// per-lane load, which the wait for the positions hides, instead of eight
+// SGPRs and the selects between them).
+__device__ __forceinline__ uint32_t pattern_bits(SysPtr S, int cls, int i)
 {
-    if (frozen) {
-        const float2 w = omega[cell_off + cell];
-        return t ? w.y : w.x;
-    }
-    return omega_of(f, load_counts<CW>(cnt, cell_off + cell), t);
-}
-
-// Bead type from the system's 128-bit pattern.  All pattern words are loaded
-// as values and selected by value: a per-lane choice between word addresses
-// compiled (gfx950, -O3) into divergent branches that left the address of
-// the fourth word unset for beads 96..127.
-__device__ __forceinline__ int pattern_type(const DevSys &S, int cls, int i)
-{
-    const uint4 pa = *reinterpret_cast<const uint4 *>(S.pat_a);
-    const uint4 pb = *reinterpret_cast<const uint4 *>(S.pat_b);
-    const bool use_a = cls == 0;
-    const uint32_t x = use_a ? pa.x : pb.x, y = use_a ? pa.y : pb.y;
-    const uint32_t z = use_a ? pa.z : pb.z, w = use_a ? pa.w : pb.w;
-    const int k = i >> 5;
-    const uint32_t lo = (k & 1) ? y : x, hi = (k & 1) ? w : z;
-    const uint32_t word = (k & 2) ? hi : lo;
-    return (int)((word >> (i & 31)) & 1u);
+    const uint32_t off = (uint32_t)(cls * 4 + (i >> 5)) << 2;
+    return ld_off<uint32_t>((const void *)(uintptr_t)S->pat_a, off) >> (i & 31);
 }
 
 // Class of a chain (which pattern it carries): from the class array when
 // conversion zones (or the caller) change classes, else chains
 // [0, n_chains_a) are class a.
 template <bool CPL = true>
-__device__ __forceinline__ int chain_cls(const DevSys &S, const uint8_t *cc, uint32_t clog)
+__device__ __forceinline__ int chain_cls(SysPtr S, const uint8_t *cc, uint32_t clog)
 {
     if constexpr (CPL)
-        if (S.cls_array) return (int)cc[S.chain_off + clog];
-    return (int)clog < S.n_chains_a ? 0 : 1;
+        if (S->cls_array) return (int)cc[S->chain_off + clog];
+    return (int)clog < S->n_chains_a ? 0 : 1;
 }
 
-// Unwrapped z cell of a bead, as computed by locate/step.
-__device__ __forceinline__ int zcell(const CellPos &c, const BeadF32 &) { return (int)c.fz; }
-__device__ __forceinline__ int zcell(const CellPos &c, const BeadCell &) { return (int)c.fz; }
-
-// Types of beads i (even) and i + 1, from one pattern word.
-__device__ __forceinline__ void pattern_pair(const DevSys &S, int cls, int i, int &t0, int &t1)
+// The arguments that lead to the position loads, read together: a wave waits
+// once for them, once for its tile (with the sweep counter and the tile's
+// acceptance count) and then issues its position loads.  (Read where they
+// are used, these are six dependent scalar loads, 1900 to 4000 cycles of a
+// wave's 13000 to 23000.)
+struct Head {
+    const Tile *tiles;
+    const uint64_t *ctr;
+    const DevSys *systems;
+    unsigned long long *acc_tile;
+    int n_tiles, waves_per_block, remap;
+    uint32_t rel;
+    const uint32_t *chain_id;
+    PosArrays pos;
+};
+__device__ __forceinline__ Head head_of(ArgPtr a, bool cells)
 {
-    const uint4 pa = *reinterpret_cast<const uint4 *>(S.pat_a);
-    const uint4 pb = *reinterpret_cast<const uint4 *>(S.pat_b);
-    const bool use_a = cls == 0;
-    const uint32_t x = use_a ? pa.x : pb.x, y = use_a ? pa.y : pb.y;
-    const uint32_t z = use_a ? pa.z : pb.z, w = use_a ? pa.w : pb.w;
-    const int k = i >> 5;
-    const uint32_t lo = (k & 1) ? y : x, hi = (k & 1) ? w : z;
-    const uint32_t word = ((k & 2) ? hi : lo) >> (i & 31);
-    t0 = (int)(word & 1u);
-    t1 = (int)((word >> 1) & 1u);
+    Head h{a->wtiles, a->sweep_ctr, a->systems, a->acc_tile, a->n_wtiles, a->waves_per_block, a->remap_blocks, a->rel,
+           a->chain_id, pos_arrays(a)};
+    asm volatile("" : "+s"(h.tiles), "+s"(h.ctr), "+s"(h.systems), "+s"(h.acc_tile), "+s"(h.n_tiles),
+                      "+s"(h.waves_per_block), "+s"(h.remap), "+s"(h.rel), "+s"(h.chain_id), "+s"(h.pos.P0),
+                      "+s"(h.pos.P1), "+s"(h.pos.P2));
+    if (cells) asm volatile("" : "+s"(h.pos.C0), "+s"(h.pos.C1), "+s"(h.pos.C2));
+    return h;
 }
 
-__device__ __forceinline__ int wave_tile(int waves_per_block, int xcd_remap)
+// Workgroups are dispatched round-robin over the 8 XCDs; the remap gives each
+// XCD a contiguous range of tiles, so its L2 sees a compact cell range.
+__device__ __forceinline__ int block_index(int remap)
 {
-    int bid = (int)blockIdx.x;
-    if (xcd_remap) {
-        // Workgroups are dispatched round-robin over the 8 XCDs; give each
-        // XCD a contiguous range of tiles so its L2 sees a compact cell range.
-        const int nb = (int)gridDim.x;
-        const int full = nb & ~7;
-        if (bid < full) bid = (bid & 7) * (full >> 3) + (bid >> 3);
-    }
-    // wave-uniform by construction; readfirstlane lets the tile and system
-    // tables be read with scalar loads
-    return __builtin_amdgcn_readfirstlane(bid * waves_per_block + (int)(threadIdx.x >> 6));
+    const int bid = (int)blockIdx.x;
+    return bid < remap ? (bid & 7) * (remap >> 3) + (bid >> 3) : bid;
 }
 
-// Block tiles: workgroup b takes tile b (the same XCD-aware remap as wave
-// tiles); a block tile packs whole chains across all waves of the block.
-__device__ __forceinline__ int block_tile(int xcd_remap)
-{
-    int bid = (int)blockIdx.x;
-    if (xcd_remap) {
-        const int nb = (int)gridDim.x;
-        const int full = nb & ~7;
-        if (bid < full) bid = (bid & 7) * (full >> 3) + (bid >> 3);
-    }
-    return __builtin_amdgcn_readfirstlane(bid);
-}
-
-// Tiling of the sweep.  Wave tiles (BT = false): a tile is G = floor(64/P)
-// whole chains on the lanes of one wave.  Block tiles (BT = true): a tile is
-// floor(64 W / P) whole chains packed over the 64 W lanes of a block, so a
-// chain may span two waves (fewer idle lanes when 64 is not a multiple of
-// P); bond neighbours across a wave boundary go through LDS.
-template <bool BT>
-__device__ __forceinline__ const Tile *tile_table(const SweepArgs &a) { return BT ? a.ptiles : a.tiles; }
-template <bool BT>
-__device__ __forceinline__ int tile_lane() { return BT ? (int)threadIdx.x : (int)(threadIdx.x & 63); }
-// chains per tile; (64 W + 1/2) / P is at least 1/(2P) from an integer
-template <bool BT>
-__device__ __forceinline__ int tile_capacity(const DevSys &S)
-{
-    return BT ? (int)(((float)blockDim.x + 0.5f) * S.inv_P) : S.G;
-}
-
-__device__ __forceinline__ SysView make_view(const DevSys &S)
-{
-    SysView v;
-    v.n0 = S.n[0]; v.n1 = S.n[1]; v.n2 = S.n[2];
-    v.inv_n0 = S.inv_n[0]; v.inv_n1 = S.inv_n[1]; v.inv_n2 = S.inv_n[2];
-    v.e0 = S.edge[0]; v.e1 = S.edge[1]; v.e2 = S.edge[2];
-    v.ie0 = S.inv_edge[0]; v.ie1 = S.inv_edge[1]; v.ie2 = S.inv_edge[2];
-    v.dyadic = S.edge_dyadic != 0;
-    return v;
-}
-
-__device__ __forceinline__ float dot3(float3 a, float3 b) { return fmaf(a.x, b.x, fmaf(a.y, b.y, a.z * b.z)); }
-__device__ __forceinline__ float3 add3(float3 a, float3 b) { return make_float3(a.x + b.x, a.y + b.y, a.z + b.z); }
-
-// ---------------------------------------------------------------------------
-// The sweep kernel: even pass, odd pass, density update (and, in density
-// mode 1, the fold of the previous delta).  One launch per sweep for every
-// system.
-// ---------------------------------------------------------------------------
-// Load the positions of one wave tile (lane p of chain g holds beads 2p and
-// 2p+1).
-template <bool BT, class Bead>
-__device__ __forceinline__ void tile_load(const SweepArgs &a, int tile, Bead &b0, Bead &b1, uint32_t &clog)
-{
-    const Tile T = tile_table<BT>(a)[tile];
-    const DevSys &S = a.systems[T.sys];
-    const int P = S.P;
-    const int lane = tile_lane<BT>();
-    const int g = (int)(((float)lane + 0.5f) * S.inv_P);
-    const int p = lane - g * P;
-    const int nin = min(tile_capacity<BT>(S), S.n_chains - (int)T.chain0);
-    const bool active = g < nin;
-    // the logical chain id keys the random numbers: load it with the
-    // positions, so the draws do not wait for a second memory round trip
-    clog = a.chain_id[S.chain_off + (int)T.chain0 + (active ? g : 0)];
-    b0 = Bead{};
-    b1 = Bead{};
-    if (active) {
-        const int64_t slot = S.slot_off + (int64_t)((int)T.chain0 + g) * (2 * P) + 2 * p;
-        load_pair(PosArrays{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2}, slot, b0, b1);
-    }
-}
-
-// One wave tile of the sweep: the even pass, the odd pass and the density
-// delta of up to G whole chains, from positions already loaded by tile_load.
-// Face fluxes of one bead that moved from cell o to cell n (wrapped
-// coordinates, at most one step per axis): the move is taken axis by axis,
-// x, y, then z, and each step adds the bead to the flux through one face:
-// F_a(c) counts the beads that crossed from c to c + e_a, so a step -1 from
-// c subtracts one from F_a(c - e_a).  Flux word of face (a, c) for type t:
-// a W + word(c, t).
-template <int CW>
-__device__ __forceinline__ uint32_t emit_faces(uint32_t *list, uint32_t len, int64_t W, int64_t cell_off, CellPos o,
-                                               const CellPos &n, int t, bool on, const SysView &v)
-{
-    const uint32_t inc = count_inc<CW>(t);
-    // x
-    {
-        const int k = n.x == o.x ? 0 : (n.x == wrap_step(o.x + 1, v.n0) ? 1 : -1);
-        CellPos f = o;
-        if (k < 0) f.x = n.x;
-        len = list_push(list, len, on && k != 0, (uint32_t)count_word<CW>(cell_off + lin(f, v), t), k > 0 ? inc : 0u - inc);
-        o.x = n.x;
-    }
-    // y
-    {
-        const int k = n.y == o.y ? 0 : (n.y == wrap_step(o.y + 1, v.n1) ? 1 : -1);
-        CellPos f = o;
-        if (k < 0) f.y = n.y;
-        len = list_push(list, len, on && k != 0, (uint32_t)(W + count_word<CW>(cell_off + lin(f, v), t)),
-                        k > 0 ? inc : 0u - inc);
-        o.y = n.y;
-    }
-    // z
-    {
-        const int k = n.z == o.z ? 0 : (n.z == wrap_step(o.z + 1, v.n2) ? 1 : -1);
-        CellPos f = o;
-        if (k < 0) f.z = n.z;
-        len = list_push(list, len, on && k != 0, (uint32_t)(2 * W + count_word<CW>(cell_off + lin(f, v), t)),
-                        k > 0 ? inc : 0u - inc);
-    }
-    return len;
-}
-
-// End of a tile: the density change of the beads whose (cell, type)
-// changed -- cell words (density modes 0, 1, 3) or face fluxes (mode 2) --
-// merged per wave in LDS, then one device atomic per distinct word with a
-// nonzero sum; the acceptance count (into the tile's own counter when
-// a.acc_tile is set: acc_prev + this sweep's count) and the cell-range
-// status.  Bead j moved from cell o_j with type t_j to cell f_j with type u_j
-// (u_j != t_j only for a chain converted in a boundary zone, never in mode
-// 2); m_j says that something changed.
-template <int CW, int DM>
-__device__ __forceinline__ void tile_finish(const SweepArgs &a, int wave, uint32_t sys, int64_t cell_off,
-                                            const SysView &v, uint32_t *dcur, uint32_t *list,
-                                            uint8_t *tab, bool m0, const CellPos &o0, const CellPos &f0,
-                                            int t0, int u0, bool m1, const CellPos &o1, const CellPos &f1, int t1,
-                                            int u1, bool acc0, bool acc1, bool bad, unsigned long long acc_prev)
-{
-    const int lane = (int)(threadIdx.x & 63);
-    uint32_t n = 0;
-    if constexpr (DM == 2) {
-        n = emit_faces<CW>(list, n, a.count_words, cell_off, o0, f0, t0, m0, v);
-        n = emit_faces<CW>(list, n, a.count_words, cell_off, o1, f1, t1, m1, v);
-    } else {
-        n = list_push2(list, n, m0, count_word<CW>(cell_off + lin(o0, v), t0), 0u - count_inc<CW>(t0),
-                       count_word<CW>(cell_off + lin(f0, v), u0), count_inc<CW>(u0));
-        n = list_push2(list, n, m1, count_word<CW>(cell_off + lin(o1, v), t1), 0u - count_inc<CW>(t1),
-                       count_word<CW>(cell_off + lin(f1, v), u1), count_inc<CW>(u1));
-    }
-    list_flush(list, tab, n, dcur);
-
-    const uint64_t nacc = __popcll(__ballot(acc0)) + __popcll(__ballot(acc1));
-    const bool any_bad = __ballot(bad) != 0;
-    if (lane == 0) {
-        if (nacc && a.acc_tile)   // this wave owns tile `wave` for the sweep
-            a.acc_tile[wave] = acc_prev + nacc;
-        else if (nacc)
-            atomicAdd(a.accept + ((int64_t)sys * kAcceptSlots + (wave % kAcceptSlots)) * kAcceptStride,
-                      (unsigned long long)nacc);
-        if (any_bad) atomicOr(a.status, ST_CELL_OVERFLOW);
-    }
-}
-
-// Boundary-zone conversion (Sec. 3.2, "Coupling"), after the moves of a
-// sweep: a chain whose binned centre -- the mean of its beads' z-cell
-// indexes, compared as the exact integer sum -- lies in the lower zone
-// becomes class a, in the upper zone class b.  zf0, zf1: the final z cells of
-// this lane's beads.  Returns the chain's new class; the chain's first lane
-// stores it and the wave counts the conversions.
-__device__ __forceinline__ int zone_convert(const SweepArgs &a, const DevSys &S, uint32_t sys, uint32_t clog,
-                                            int cls, bool active, int p, int P, bool has1, int zf0, int zf1)
-{
-    const int lane = (int)(threadIdx.x & 63);
-    int z = active ? zf0 + (has1 ? zf1 : 0) : 0;
-    // segmented sum over the chain's P lanes: lane p ends with the sum over
-    // [p, P) of its chain, so the chain's first lane holds the total
-    for (int o = 1; o < 64; o <<= 1) {
-        const int w = __shfl_down(z, o);
-        if (p + o < P) z += w;
-    }
-    const int sum = __shfl(z, lane - p);
-    int nc = cls;
-    if (S.zone_a && sum < S.zone_a_lim) nc = 0;
-    else if (S.zone_b && sum >= S.zone_b_lim) nc = 1;
-    const bool conv = active && p == 0 && nc != cls;
-    if (conv) a.chain_class[S.chain_off + clog] = (uint8_t)nc;
-    const uint64_t to_a = __popcll(__ballot(conv && nc == 0)), to_b = __popcll(__ballot(conv && nc == 1));
-    if (lane == 0) {
-        if (to_a) atomicAdd(a.conv + 2 * sys, (unsigned long long)to_a);
-        if (to_b) atomicAdd(a.conv + 2 * sys + 1, (unsigned long long)to_b);
-    }
-    return active ? nc : cls;
-}
-
-// Trial position outside the walls (z cell outside [wall_lo, wall_hi)).
-__device__ __forceinline__ bool outside_walls(const DevSys &S, int zc)
-{
-    return S.walls && (zc < S.wall_lo || zc >= S.wall_hi);
-}
-
-// Umbrella part of the field difference of a bead of type t between its
-// trial and its old cell: -lambda/N (target_t(new) - target_t(old)).
-__device__ __forceinline__ float umb_step(float coef, float2 tn, float2 to, int t)
-{
-    return coef * (t ? to.y - tn.y : to.x - tn.x);
-}
-
-template <int R, int CW, int DM, bool CPL, bool BT, class Bead>
-__device__ __forceinline__ void sweep_tile(const SweepArgs &a, int wave, uint64_t s, const uint32_t *cin,
-                                           const uint32_t *dprev, uint32_t *dcur, uint32_t *list,
-                                           uint8_t *tab, Bead b0, Bead b1, uint32_t clog,
-                                           unsigned long long acc_prev = 0ull)
-{
-    const Tile T = tile_table<BT>(a)[wave];
-    const DevSys &S = a.systems[T.sys];
-    // per-system scalars, read once at the top so that divergent code below
-    // keeps them in SGPRs instead of re-reading the table
-    const SysView v = make_view(S);
-    const FieldCoef fc{S.cAA, S.cAB, S.cBA, S.cBB, S.c0};
-    const bool frozen = S.frozen != 0;
-    const int64_t cell_off = S.cell_off;
-    const int N = S.N, P = S.P;
-    const int lane = tile_lane<BT>();
-    // lane / P: (lane + 1/2) / P is at least 1/(2P) from an integer, far more
-    // than the FP32 error of the product
-    const int g = (int)(((float)lane + 0.5f) * S.inv_P);
-    const int p = lane - g * P;
-    const int nin = min(tile_capacity<BT>(S), S.n_chains - (int)T.chain0);
-    const bool active = g < nin;
-    const int chain = (int)T.chain0 + (active ? g : 0);
-    const int i0 = 2 * p, i1 = 2 * p + 1;
-    const bool has1 = active && i1 < N;
-    const int64_t slot = S.slot_off + (int64_t)chain * (2 * P) + i0;
-    const PosArrays A{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2};
-    const Bead ob0 = b0, ob1 = b1;   // the stored state, to write back only what changes
-
-    // logical chain id: keys the random numbers and picks the species, so
-    // results do not depend on where a chain sits in memory
-    const int cls = chain_cls<CPL>(S, a.chain_class, clog);
-    int t0, t1;
-    pattern_pair(S, cls, i0, t0, t1);
-    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-    const float delta_s = S.delta * 0x1p-23f;
-    const Draw d0 = move_draw((uint32_t)i0, clog, (uint32_t)s, S.sys_id, k0, k1, delta_s);
-    const Draw d1 = move_draw((uint32_t)i1, clog, (uint32_t)s, S.sys_id, k0, k1, delta_s);
-    bool bad = false;
-    const CellPos c0 = locate(b0, v, bad);
-    const CellPos c1 = locate(b1, v, bad);
-    const int old0 = lin(c0, v);
-    const int old1 = lin(c1, v);
-
-    // Both trial positions are known before either pass (the odd bead's
-    // proposal does not depend on the even pass), so the fields of all four
-    // cells are gathered together: one memory latency instead of two.
-    const Bead n0 = propose(b0, d0, v);
-    const Bead n1 = propose(b1, d1, v);
-    const CellPos s0 = step(c0, b0, n0, v), s1 = step(c1, b1, n1, v);
-    const int nc0 = lin(s0, v);
-    const int nc1 = lin(s1, v);
-    // walls: a trial position outside the slab is rejected (and needs no field)
-    const bool out0 = CPL && outside_walls(S, zcell(s0, n0)), out1 = CPL && outside_walls(S, zcell(s1, n1));
-    const bool g0 = active && nc0 != old0 && !out0, g1 = has1 && nc1 != old1 && !out1;
-    float dw0 = 0.0f, dw1 = 0.0f;
-    if (frozen) {
-        float2 wn0{0.f, 0.f}, wo0{0.f, 0.f}, wn1{0.f, 0.f}, wo1{0.f, 0.f};
-        if (g0) { wn0 = a.omega[cell_off + nc0]; wo0 = a.omega[cell_off + old0]; }
-        if (g1) { wn1 = a.omega[cell_off + nc1]; wo1 = a.omega[cell_off + old1]; }
-        dw0 = t0 ? wn0.y - wo0.y : wn0.x - wo0.x;
-        dw1 = t1 ? wn1.y - wo1.y : wn1.x - wo1.x;
-    } else {
-        RawCount rn0{0u, 0u, 0u, 0u}, ro0{0u, 0u, 0u, 0u}, rn1{0u, 0u, 0u, 0u}, ro1{0u, 0u, 0u, 0u};
-        if (g0) {
-            rn0 = load_raw<CW, DM == 1>(cin, dprev, cell_off + nc0);
-            ro0 = load_raw<CW, DM == 1>(cin, dprev, cell_off + old0);
-        }
-        if (g1) {
-            rn1 = load_raw<CW, DM == 1>(cin, dprev, cell_off + nc1);
-            ro1 = load_raw<CW, DM == 1>(cin, dprev, cell_off + old1);
-        }
-        float2 un0{0.f, 0.f}, uo0{0.f, 0.f}, un1{0.f, 0.f}, uo1{0.f, 0.f};
-        const bool umb = CPL && S.umb != 0;
-        if (umb) {
-            if (g0) { un0 = a.tgt[cell_off + nc0]; uo0 = a.tgt[cell_off + old0]; }
-            if (g1) { un1 = a.tgt[cell_off + nc1]; uo1 = a.tgt[cell_off + old1]; }
-        }
-        if (g0) dw0 = omega_of(fc, counts_of<CW>(rn0), t0) - omega_of(fc, counts_of<CW>(ro0), t0);
-        if (g1) dw1 = omega_of(fc, counts_of<CW>(rn1), t1) - omega_of(fc, counts_of<CW>(ro1), t1);
-        if (umb) {
-            dw0 += umb_step(S.umb_coef, un0, uo0, t0);
-            dw1 += umb_step(S.umb_coef, un1, uo1, t1);
-        }
-    }
-    const float kh = S.k_half;
-
-    // even pass: bead 2p, neighbours 2p-1 (previous lane's odd bead) and 2p+1.
-    // dE_b = (k/2) sum_j [2 d.(r - r_j) + |d|^2] = (k/2) [2 d.sum_j (r - r_j) + n_j |d|^2]
-    bool acc0;
-    {
-        const Bead left = left_neighbour<BT>(b1);
-        const float3 de = bond(n0, b0, v);
-        const float3 zero = make_float3(0.0f, 0.0f, 0.0f);
-        const float3 bl = p > 0 ? bond(b0, left, v) : zero, br = i1 < N ? bond(b0, b1, v) : zero;
-        const float nj = (p > 0 ? 1.0f : 0.0f) + (i1 < N ? 1.0f : 0.0f);
-        const float dE = fmaf(fmaf(2.0f, dot3(de, add3(bl, br)), nj * dot3(de, de)), kh, dw0);
-        acc0 = active && !out0 && (d0.u < __expf(-dE));
-        if (acc0) b0 = n0;
-    }
-    // odd pass: bead 2p+1, neighbours 2p (this lane, updated) and 2p+2 (next lane)
-    bool acc1;
-    {
-        const Bead right = right_neighbour<BT>(b0);
-        const float3 de = bond(n1, b1, v);
-        const float3 br = i1 + 1 < N ? bond(b1, right, v) : make_float3(0.0f, 0.0f, 0.0f);
-        const float nj = i1 + 1 < N ? 2.0f : 1.0f;
-        const float dE = fmaf(fmaf(2.0f, dot3(de, add3(bond(b1, b0, v), br)), nj * dot3(de, de)), kh, dw1);
-        acc1 = has1 && !out1 && (d1.u < __expf(-dE));
-        if (acc1) b1 = n1;
-    }
-    if (active) store_moved(A, slot, b0, b1, ob0, ob1, acc0 || acc1);
-    // final cells: without coupling a change implies an accepted move, so the
-    // trial cells serve (and the selection costs no registers)
-    const CellPos f0 = CPL ? (acc0 ? s0 : c0) : s0, f1 = CPL ? (acc1 ? s1 : c1) : s1;
-    int u0 = t0, u1 = t1;
-    if (CPL && !BT && S.zones) {   // (the host never packs contexts with zones)
-        const int ncls = zone_convert(a, S, T.sys, clog, cls, active, p, P, has1, zcell(f0, b0), zcell(f1, b1));
-        pattern_pair(S, ncls, i0, u0, u1);
-    }
-    tile_finish<CW, DM>(a, BT ? wave * 16 + (int)(threadIdx.x >> 6) : wave, T.sys, cell_off, v, dcur, list, tab,
-                        active && ((acc0 && nc0 != old0) || u0 != t0), c0, f0, t0, u0,
-                        has1 && ((acc1 && nc1 != old1) || u1 != t1), c1, f1, t1, u1, acc0, acc1, active && bad, acc_prev);
-}
-
-// ---------------------------------------------------------------------------
-// Stream tiles (uniform moves, no coupling)
-// ---------------------------------------------------------------------------
-// The lanes of a system form one stream in chain order (chain c holds lanes
+// Tiling of the sweep.  Wave tiles: a tile is G = floor(64/P) whole chains on
+// the lanes of one wave.  Block tiles: a tile is floor(64 W / P) whole chains
+// packed over the 64 W lanes of a block, so a chain may span two waves (fewer
+// idle lanes when 64 is not a multiple of P); bond neighbours across a wave
+// boundary go through LDS.  Stream tiles (uniform moves, no coupling): the
+// lanes of a system form one stream in chain order (chain c holds lanes
 // [c P, (c + 1) P)), so chains run across wave boundaries and no lane idles
 // but in a system's last wave.  Wave w moves the 62 stream lanes
 // [62 w, 62 w + 62) on its lanes 1..62; lane 0 holds the stream lane before
@@ -1026,181 +742,459 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs &a, int wave, uint64_
 // that owns it, so the same decision.  The owners of the two overlap lanes
 // rewrite them during the same sweep, so the overlap lanes read them from
 // the halo copy taken before the sweep (halo_index): tile w - 1's last and
-// tile w + 1's first owned lane.  A stream tile names its system (low 24
-// bits), the pair index of its first owned lane within that lane's chain
-// (high 8 bits) and that chain.
-__device__ __forceinline__ uint32_t stile_sys(const Tile &T) { return T.sys & 0xFFFFFFu; }
+// tile w + 1's first owned lane.
+constexpr int TIL_WAVE = 0, TIL_BLOCK = 1, TIL_STREAM = 2;
 
-struct StreamLane {
-    int chain, p;
+template <int TIL>
+__device__ __forceinline__ int tile_lane() { return TIL == TIL_BLOCK ? (int)threadIdx.x : (int)(threadIdx.x & 63); }
+
+struct TileLane {
+    int g, p;       // the lane holds beads 2p and 2p + 1 of chain chain0 + g
     bool valid;     // a bead pair of the system: takes every step
     bool own;       // and belongs to this wave: stores and counts
 };
 
-__device__ __forceinline__ StreamLane stream_lane(const Tile &T, const DevSys &S, int lane)
+template <int TIL>
+__device__ __forceinline__ TileLane lane_of(const Tile &T)
 {
-    const int P = S.P;
-    // stream lane 62 w - 1 + lane, as (chain0 - 1 + gr, q - gr P) with q >= 0
-    const int q = (int)(T.sys >> 24) + lane - 1 + P;            // < 2 P + 63
-    const int gr = (int)(((float)q + 0.5f) * S.inv_P);
-    StreamLane L;
-    L.chain = (int)T.chain0 - 1 + gr;
-    L.p = q - gr * P;
-    L.valid = L.chain >= 0 && L.chain < S.n_chains;
-    L.own = L.valid && lane >= 1 && lane <= kStreamLanes;
+    const int lane = tile_lane<TIL>(), P = (int)(T.lanes >> 11 & 127u), n = (int)(T.lanes & 2047u);
+    const int q = TIL == TIL_STREAM ? (int)(T.lanes >> 24) + lane : lane;
+    TileLane L;
+    // q / P: (q + 1/2) / P is at least 1/(2P) from an integer, far more than
+    // the FP32 error of the product (q < 1024)
+    L.g = (int)(((float)q + 0.5f) * T.inv_P);
+    L.p = q - L.g * P;
+    L.valid = lane < n && (TIL != TIL_STREAM || lane > 0 || (T.lanes >> 18 & 1u));
+    L.own = TIL == TIL_STREAM ? lane >= 1 && lane <= kStreamLanes && lane < n : L.valid;
     return L;
 }
 
+// The tile tables (see Tile), one thread per tile.
+__global__ __launch_bounds__(256) void k_make_tiles(MakeTilesArgs a)
+{
+    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t >= a.n_tiles) return;
+    int lo = 0, hi = a.n_sys - 1;            // the system with first[lo] <= t < first[lo + 1]
+    while (lo < hi) {
+        const int mid = lo + (hi - lo + 1) / 2;
+        if (a.first[mid] <= t) lo = mid;
+        else hi = mid - 1;
+    }
+    const DevSys &S = a.systems[lo];
+    const int64_t w = t - a.first[lo];
+    const int P = S.P;
+    Tile T;
+    T.sys = (uint32_t)lo;
+    T.inv_P = S.inv_P;
+    if (a.kind == 2) {
+        // stream lane 62 w sits on lane 1; lane 0's pair is one before it
+        const int64_t l0 = w * kStreamLanes, left = (int64_t)S.n_chains * P - l0;
+        const int64_t c = l0 / P;
+        T.chain0 = (int32_t)(c - 1);
+        T.slot = S.slot_off + 2 * (l0 - 1);
+        T.lanes = tile_word((uint32_t)(left + 1 < 64 ? left + 1 : 64), (uint32_t)P, w > 0, (uint32_t)(l0 - c * P + P - 1));
+    } else {
+        const int G = a.kind == 1 ? a.lanes / P : S.G;
+        T.chain0 = (int32_t)(w * G);
+        const int n = S.n_chains - T.chain0 < G ? S.n_chains - T.chain0 : G;
+        T.slot = S.slot_off + (int64_t)T.chain0 * (2 * P);
+        T.lanes = tile_word((uint32_t)(n * P), (uint32_t)P, true, 0u);
+    }
+    T.chain = S.chain_off + T.chain0;
+    a.tiles[t] = T;
+}
+
+__device__ __forceinline__ SysView make_view(SysPtr S)
+{
+    SysView v;
+    v.n0 = S->n[0]; v.n1 = S->n[1]; v.n2 = S->n[2];
+    v.e0 = S->edge[0]; v.e1 = S->edge[1]; v.e2 = S->edge[2];
+    v.ie0 = S->inv_edge[0]; v.ie1 = S->inv_edge[1]; v.ie2 = S->inv_edge[2];
+    v.dyadic = S->edge_dyadic != 0;
+    return v;
+}
+
+__device__ __forceinline__ float dot3(float3 a, float3 b) { return fmaf(a.x, b.x, fmaf(a.y, b.y, a.z * b.z)); }
+__device__ __forceinline__ float3 add3(float3 a, float3 b) { return make_float3(a.x + b.x, a.y + b.y, a.z + b.z); }
+
+// ---------------------------------------------------------------------------
+// The sweep kernel: even pass, odd pass, density update (and, in density
+// mode 1, the fold of the previous delta).  One launch per sweep for every
+// system.
+// ---------------------------------------------------------------------------
+// The count words a sweep's field gathers read and the words its changes go
+// to, by density mode.  Mode 1: the counts of sweep s are B[s-1] + D[s-1];
+// this sweep adds to D[s], writes B[s] and clears D[s+1] (last read by sweep
+// s-1).  Mode 2: the face fluxes of sweep s go to flux buffer s mod 2 (three
+// W-word arrays).  Mode 3: the counts are B[s mod 2]; the changes go straight
+// into its mirror B[(s+1) mod 2], which holds the same counts when the sweep
+// starts and is read by no gather of this sweep.
+template <int DM>
+__device__ __forceinline__ const uint32_t *counts_in(ArgPtr a, uint64_t s)
+{
+    return DM == 1 ? a->base + ((s + 1) & 1) * a->count_words : (DM == 3 ? a->base + (s & 1) * a->count_words : a->base);
+}
+template <int DM>
+__device__ __forceinline__ const uint32_t *delta_in(ArgPtr a, uint64_t s)
+{
+    return DM == 1 ? a->delta + ((s + 2) % 3) * a->count_words : nullptr;
+}
+template <int DM>
+__device__ __forceinline__ uint32_t *changes_out(ArgPtr a, uint64_t s)
+{
+    return DM == 1   ? a->delta + (s % 3) * a->count_words
+           : DM == 2 ? a->flux + (s & 1) * 3 * a->count_words
+           : DM == 3 ? a->base + ((s + 1) & 1) * a->count_words
+                     : a->delta;
+}
+
 // One bead pair in the halo: component k of both beads in one 8-byte word,
-// the components of one side contiguous (16-byte accesses).
-__device__ __forceinline__ void halo_put(uint2 *h, int buf, int64_t tile, int side, int64_t cap, const BeadF32 &a,
-                                         const BeadF32 &b)
+// the components of one side contiguous (16-byte accesses).  h: the entry of
+// the wave's tile; off: byte offset of the side from there.
+__device__ __forceinline__ void halo_put(uint2 *h, uint32_t off, const BeadF32 &a, const BeadF32 &b)
 {
-    uint2 *e = h + halo_index(buf, 0, tile, side, cap);
-    *reinterpret_cast<uint4 *>(e) = make_uint4(__float_as_uint(a.x), __float_as_uint(b.x), __float_as_uint(a.y),
-                                               __float_as_uint(b.y));
-    e[2] = make_uint2(__float_as_uint(a.z), __float_as_uint(b.z));
+    st_off(h, off, u4{__float_as_uint(a.x), __float_as_uint(b.x), __float_as_uint(a.y), __float_as_uint(b.y)});
+    st_off(h, off + 16, u2{__float_as_uint(a.z), __float_as_uint(b.z)});
 }
-__device__ __forceinline__ void halo_put(uint2 *h, int buf, int64_t tile, int side, int64_t cap, const BeadCell &a,
-                                         const BeadCell &b)
+__device__ __forceinline__ void halo_put(uint2 *h, uint32_t off, const BeadCell &a, const BeadCell &b)
 {
-    uint4 *e = reinterpret_cast<uint4 *>(h + halo_index(buf, 0, tile, side, cap));
-    e[0] = make_uint4(__float_as_uint(a.ox), __float_as_uint(b.ox), __float_as_uint(a.oy), __float_as_uint(b.oy));
-    e[1] = make_uint4(__float_as_uint(a.oz), __float_as_uint(b.oz), (uint32_t)a.cx, (uint32_t)b.cx);
-    e[2] = make_uint4((uint32_t)a.cy, (uint32_t)b.cy, (uint32_t)a.cz, (uint32_t)b.cz);
+    st_off(h, off, u4{__float_as_uint(a.ox), __float_as_uint(b.ox), __float_as_uint(a.oy), __float_as_uint(b.oy)});
+    st_off(h, off + 16, u4{__float_as_uint(a.oz), __float_as_uint(b.oz), (uint32_t)a.cx, (uint32_t)b.cx});
+    st_off(h, off + 32, u4{(uint32_t)a.cy, (uint32_t)b.cy, (uint32_t)a.cz, (uint32_t)b.cz});
 }
-__device__ __forceinline__ void halo_get(const uint2 *h, int buf, int64_t tile, int side, int64_t cap, BeadF32 &a,
-                                         BeadF32 &b)
+// (read as one 8-byte load per component, like the pairs of the position
+// arrays, so both kinds of lanes load into the same registers and the wave
+// waits once for all of them)
+__device__ __forceinline__ void halo_get(const uint2 *h, uint32_t off, BeadF32 &a, BeadF32 &b)
 {
-    const uint2 *e = h + halo_index(buf, 0, tile, side, cap);
-    const uint4 xy = *reinterpret_cast<const uint4 *>(e);
-    const uint2 z = e[2];
-    a = BeadF32{__uint_as_float(xy.x), __uint_as_float(xy.z), __uint_as_float(z.x)};
-    b = BeadF32{__uint_as_float(xy.y), __uint_as_float(xy.w), __uint_as_float(z.y)};
+    const f2 x = ld_off<f2>(h, off), y = ld_off<f2>(h, off + 8), z = ld_off<f2>(h, off + 16);
+    a = BeadF32{x.x, y.x, z.x};
+    b = BeadF32{x.y, y.y, z.y};
 }
-__device__ __forceinline__ void halo_get(const uint2 *h, int buf, int64_t tile, int side, int64_t cap, BeadCell &a,
-                                         BeadCell &b)
+__device__ __forceinline__ void halo_get(const uint2 *h, uint32_t off, BeadCell &a, BeadCell &b)
 {
-    const uint4 *e = reinterpret_cast<const uint4 *>(h + halo_index(buf, 0, tile, side, cap));
-    const uint4 u = e[0], v = e[1], w = e[2];
-    a = BeadCell{(int)v.z, (int)w.x, (int)w.z, __uint_as_float(u.x), __uint_as_float(u.z), __uint_as_float(v.x)};
-    b = BeadCell{(int)v.w, (int)w.y, (int)w.w, __uint_as_float(u.y), __uint_as_float(u.w), __uint_as_float(v.y)};
+    const f2 x = ld_off<f2>(h, off), y = ld_off<f2>(h, off + 8), z = ld_off<f2>(h, off + 16);
+    const i2 cx = ld_off<i2>(h, off + 24), cy = ld_off<i2>(h, off + 32), cz = ld_off<i2>(h, off + 40);
+    a = BeadCell{cx.x, cy.x, cz.x, x.x, y.x, z.x};
+    b = BeadCell{cx.y, cy.y, cz.y, x.y, y.y, z.y};
 }
+constexpr uint32_t kHaloSide = kHaloSlots * sizeof(uint2);     // bytes of one side of an entry
 
-// Owned lanes load their pairs from the position arrays; the overlap lanes
-// (valid only next to a tile of the same system: lane 0 when the tile does
-// not start its system's stream, lane 63 when the stream goes on) load them
+// Load the bead pairs of one tile and the logical chain ids, which key the
+// random numbers (with the positions, so the draws do not wait for a second
+// memory round trip).  Lanes without a pair of their own read another
+// lane's; nothing comes of it.  The overlap lanes of a stream tile (valid
+// only next to a tile of the same system: lane 0 when the tile does not
+// start its system's stream, lane 63 when the stream goes on) load theirs
 // from halo buffer s mod 2.
-template <class Bead>
-__device__ __forceinline__ void stream_load(const SweepArgs &a, int tile, uint64_t s, Bead &b0, Bead &b1,
-                                            uint32_t &clog)
+template <int TIL, class Bead>
+__device__ __forceinline__ void tile_load(ArgPtr a, const Head &h, const Tile &T, int tile, uint64_t s, Bead &b0,
+                                          Bead &b1, uint32_t &clog)
 {
-    const Tile T = a.ptiles[tile];
-    const DevSys &S = a.systems[stile_sys(T)];
-    const int lane = (int)(threadIdx.x & 63);
-    const StreamLane L = stream_lane(T, S, lane);
-    clog = a.chain_id[S.chain_off + (L.valid ? L.chain : (int)T.chain0)];
-    b0 = Bead{};
-    b1 = Bead{};
-    if (L.own)
-        load_pair(PosArrays{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2}, S.slot_off + (int64_t)L.chain * (2 * S.P) + 2 * L.p,
-                  b0, b1);
-    else if (L.valid)
-        halo_get(a.halo, (int)(s & 1), lane == 0 ? tile - 1 : tile + 1, lane == 0 ? 1 : 0, a.halo_cap, b0, b1);
+    const TileLane L = lane_of<TIL>(T);
+    // (lane 1 of a stream tile is always its own; chain0 + 1 is lane 1's chain)
+    const int back = TIL == TIL_STREAM ? 1 : 0;
+    clog = ld_off<uint32_t>(h.chain_id + T.chain, (uint32_t)(L.valid ? L.g : back) << 2);
+    const uint32_t lane = (uint32_t)tile_lane<TIL>();
+    if (TIL == TIL_STREAM && L.valid && !L.own) {
+        const uint2 *e = a->halo + halo_index((int)(s & 1), 0, tile, 0, a->halo_cap);
+        // tile - 1, side 1 for lane 0; tile + 1, side 0 for lane 63
+        halo_get(e - kHaloSlots, lane == 0 ? 0u : 3u * kHaloSide, b0, b1);
+    } else {
+        load_pair(h.pos, T.slot, (L.own ? lane : (uint32_t)back) * 8u, b0, b1);
+    }
 }
 
-template <int R, int CW, int DM, class Bead>
-__device__ __forceinline__ void sweep_tile_stream(const SweepArgs &a, int wave, uint64_t s, const uint32_t *cin,
-                                                  const uint32_t *dprev, uint32_t *dcur, uint32_t *list,
-                                                  uint8_t *tab, Bead b0, Bead b1, uint32_t clog,
-                                                  unsigned long long acc_prev)
+// Face fluxes of one bead that moved from cell o to cell n (wrapped
+// coordinates, at most one step per axis): the move is taken axis by axis,
+// x, y, then z, and each step adds the bead to the flux through one face:
+// F_a(c) counts the beads that crossed from c to c + e_a, so a step -1 from
+// c subtracts one from F_a(c - e_a).  Flux word of face (a, c) for type t:
+// a W + word(c, t).
+template <int CW>
+__device__ __forceinline__ uint32_t emit_faces(uint32_t *list, uint32_t W, CellPos o, const CellPos &n, int t, bool on,
+                                               const SysView &v)
 {
-    const Tile T = a.ptiles[wave];
-    const uint32_t sys = stile_sys(T);
-    const DevSys &S = a.systems[sys];
+    const uint32_t inc = count_inc<CW>(t);
+    uint32_t len = 0;
+    {
+        const int k = n.x == o.x ? 0 : (n.x == wrap_step(o.x + 1, v.n0) ? 1 : -1);
+        CellPos f = o;
+        if (k < 0) f.x = n.x;
+        len = list_push(list, len, on && k != 0, count_word<CW>(lin(f, v), t), k > 0 ? inc : 0u - inc);
+        o.x = n.x;
+    }
+    {
+        const int k = n.y == o.y ? 0 : (n.y == wrap_step(o.y + 1, v.n1) ? 1 : -1);
+        CellPos f = o;
+        if (k < 0) f.y = n.y;
+        len = list_push(list, len, on && k != 0, W + count_word<CW>(lin(f, v), t), k > 0 ? inc : 0u - inc);
+        o.y = n.y;
+    }
+    {
+        const int k = n.z == o.z ? 0 : (n.z == wrap_step(o.z + 1, v.n2) ? 1 : -1);
+        CellPos f = o;
+        if (k < 0) f.z = n.z;
+        len = list_push(list, len, on && k != 0, 2u * W + count_word<CW>(lin(f, v), t), k > 0 ? inc : 0u - inc);
+    }
+    return len;
+}
+
+// Records of the beads that moved (grid coordinates are below 2^15).
+__device__ __forceinline__ uint32_t face_push(uint32_t *recs, uint32_t n, bool on, const CellPos &o, const CellPos &f, int t)
+{
+    const uint64_t m = __builtin_amdgcn_ballot_w64(on);
+    if (on)
+        *reinterpret_cast<uint4 *>(recs + 4 * (n + lane_rank(m))) =
+            make_uint4((uint32_t)o.x | (uint32_t)o.y << 16, (uint32_t)o.z | (uint32_t)t << 16,
+                       (uint32_t)f.x | (uint32_t)f.y << 16, (uint32_t)f.z);
+    return n + (uint32_t)__popcll(m);
+}
+
+// End of a tile: the density change of the beads whose (cell, type)
+// changed -- cell words (density modes 0, 1, 3) or face fluxes (mode 2) --
+// merged per wave in LDS, then one device atomic per distinct word with a
+// nonzero sum; and the acceptance count (into the tile's own counter when
+// acc_tile is set: acc_prev + this sweep's count).  Bead j moved from cell o_j
+// with type t_j to cell f_j with type u_j (u_j != t_j only for a chain
+// converted in a boundary zone, never in mode 2); m_j says that something
+// changed.
+template <int CW, int DM>
+__device__ __forceinline__ void tile_finish(ArgPtr a, SysPtr S, int wave, uint32_t sys, uint64_t s, const SysView &v,
+                                            uint32_t *list, uint8_t *tab, bool m0, const CellPos &o0,
+                                            const CellPos &f0, int t0, int u0, bool m1, const CellPos &o1,
+                                            const CellPos &f1, int t1, int u1, bool acc0, bool acc1,
+                                            unsigned long long acc_prev)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t *dst = changes_out<DM>(a, s) + (CW == COUNT_U16 ? 1 : 2) * S->cell_off;
+    if constexpr (DM == 2) {
+        uint32_t *recs = list + 2 * kListFaces;
+        const uint32_t n0 = face_push(recs, 0u, m0, o0, f0, t0), n = face_push(recs, n0, m1, o1, f1, t1);
+        for (uint32_t b = 0; b < n; b += kWave) {
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            const bool on = b + lane < n;
+            const uint4 r = *reinterpret_cast<const uint4 *>(recs + 4 * (on ? b + lane : b));
+            const CellPos o{(int)(r.x & 0xFFFFu), (int)(r.x >> 16), (int)(r.y & 0xFFFFu), 0};
+            const CellPos f{(int)(r.z & 0xFFFFu), (int)(r.z >> 16), (int)r.w, 0};
+            const uint32_t len = emit_faces<CW>(list, (uint32_t)a->count_words, o, f, (int)(r.y >> 16), on, v);
+            list_flush<true>(list, tab, len, dst);
+        }
+    } else {
+        uint32_t n = list_push2(list, 0u, m0, count_word<CW>(lin(o0, v), t0), 0u - count_inc<CW>(t0),
+                                count_word<CW>(lin(f0, v), u0), count_inc<CW>(u0));
+        n = list_push2(list, n, m1, count_word<CW>(lin(o1, v), t1), 0u - count_inc<CW>(t1),
+                       count_word<CW>(lin(f1, v), u1), count_inc<CW>(u1));
+        list_flush<false>(list, tab, n, dst);
+    }
+
+    const uint64_t nacc = __popcll(__builtin_amdgcn_ballot_w64(acc0)) + __popcll(__builtin_amdgcn_ballot_w64(acc1));
+    if (lane == 0 && nacc) {
+        if (a->acc_tile)   // this wave owns tile `wave` for the sweep
+            a->acc_tile[wave] = acc_prev + nacc;
+        else
+            atomicAdd(a->accept + ((int64_t)sys * kAcceptSlots + (wave % kAcceptSlots)) * kAcceptStride,
+                      (unsigned long long)nacc);
+    }
+}
+
+// Boundary-zone conversion (Sec. 3.2, "Coupling"), after the moves of a
+// sweep: a chain whose binned centre -- the mean of its beads' z-cell
+// indexes, compared as the exact integer sum -- lies in the lower zone
+// becomes class a, in the upper zone class b.  zf0, zf1: the final z cells of
+// this lane's beads.  Returns the chain's new class; the chain's first lane
+// stores it and the wave counts the conversions.
+__device__ __forceinline__ int zone_convert(ArgPtr a, SysPtr S, uint32_t sys, uint32_t clog, int cls, bool active,
+                                            int p, bool has1, int zf0, int zf1)
+{
+    const int lane = (int)(threadIdx.x & 63), P = S->P;
+    int z = active ? zf0 + (has1 ? zf1 : 0) : 0;
+    // segmented sum over the chain's P lanes: lane p ends with the sum over
+    // [p, P) of its chain, so the chain's first lane holds the total
+    for (int o = 1; o < 64; o <<= 1) {
+        const int w = __shfl_down(z, o);
+        if (p + o < P) z += w;
+    }
+    const int sum = __shfl(z, lane - p);
+    int nc = cls;
+    if (S->zone_a && sum < S->zone_a_lim) nc = 0;
+    else if (S->zone_b && sum >= S->zone_b_lim) nc = 1;
+    const bool conv = active && p == 0 && nc != cls;
+    if (conv) a->chain_class[S->chain_off + clog] = (uint8_t)nc;
+    const uint64_t to_a = __popcll(__ballot(conv && nc == 0)), to_b = __popcll(__ballot(conv && nc == 1));
+    if (lane == 0) {
+        if (to_a) atomicAdd(a->conv + 2 * sys, (unsigned long long)to_a);
+        if (to_b) atomicAdd(a->conv + 2 * sys + 1, (unsigned long long)to_b);
+    }
+    return active ? nc : cls;
+}
+
+// Trial position outside the walls (z cell outside [wall_lo, wall_hi)).
+__device__ __forceinline__ bool outside_walls(SysPtr S, int zc)
+{
+    return S->walls && (zc < S->wall_lo || zc >= S->wall_hi);
+}
+
+// Umbrella part of the field difference of a bead of type t between its
+// trial and its old cell: -lambda/N (target_t(new) - target_t(old)).
+__device__ __forceinline__ float umb_step(float coef, float2 tn, float2 to, int t)
+{
+    return coef * (t ? to.y - tn.y : to.x - tn.x);
+}
+
+// Field differences between the trial cells nc[j] and the old cells oc[j] of
+// M beads of types t[j], where g[j]; all gathers are issued before the first
+// use.
+template <int CW, int DM, bool CPL, int M>
+__device__ __forceinline__ void field_steps(ArgPtr a, SysPtr S, uint64_t s, const int (&nc)[M], const int (&oc)[M],
+                                            const int (&t)[M], const bool (&g)[M], float (&dw)[M])
+{
+    const int64_t cell_off = S->cell_off;
+    if (S->frozen) {
+        const float2 *om = a->omega + cell_off;
+        float2 wn[M], wo[M];
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            wn[j] = wo[j] = make_float2(0.0f, 0.0f);
+            if (g[j]) { wn[j] = om[nc[j]]; wo[j] = om[oc[j]]; }
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) dw[j] = t[j] ? wn[j].y - wo[j].y : wn[j].x - wo[j].x;
+        return;
+    }
+    const uint32_t *cnt = counts_in<DM>(a, s) + (CW == COUNT_U16 ? 1 : 2) * cell_off;
+    const uint32_t *dlt = DM == 1 ? delta_in<DM>(a, s) + (CW == COUNT_U16 ? 1 : 2) * cell_off : nullptr;
+    const FieldCoef fc = field_coef(S);
+    RawCount rn[M], ro[M];
+    float2 un[M], uo[M];
+    const bool umb = CPL && S->umb != 0;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        rn[j] = ro[j] = RawCount{0u, 0u, 0u, 0u};
+        if (g[j]) {
+            rn[j] = load_raw<CW, DM == 1>(cnt, dlt, nc[j]);
+            ro[j] = load_raw<CW, DM == 1>(cnt, dlt, oc[j]);
+        }
+        if constexpr (CPL) {
+            un[j] = uo[j] = make_float2(0.0f, 0.0f);
+            if (umb && g[j]) { un[j] = a->tgt[cell_off + nc[j]]; uo[j] = a->tgt[cell_off + oc[j]]; }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        dw[j] = g[j] ? omega_of(fc, counts_of<CW>(rn[j]), t[j]) - omega_of(fc, counts_of<CW>(ro[j]), t[j]) : 0.0f;
+        if constexpr (CPL)
+            if (umb) dw[j] += umb_step(S->umb_coef, un[j], uo[j], t[j]);
+    }
+}
+
+// One tile of the sweep: the even pass, the odd pass and the density change,
+// from positions already loaded by tile_load.
+//
+// What bounds it: with FP32 positions in the 256 MB memory-side cache, vector
+// issue and the latency of one wave's chain of loads (8 waves per SIMD are the
+// most there are); with cell + offset positions beyond that cache, memory
+// (36 to 48 bytes a bead).  Hence: scalars in SGPRs but only while they are
+// needed (`later`), 32-bit lane offsets from uniform bases, one range check
+// for all four cells, DPP instead of LDS shuffles, and the head of the chain
+// read in two scalar round trips (Head, Tile).  Against a form without these
+// (64-bit lane addresses, cells one by one, scalars read at the top): 745 ->
+// 480 vector instructions a wave for FP32, 967 -> 590 for cell + offset;
+// 4.2M beads FP32 59.7 -> 56.1 us a sweep, 124.6M beads cell + offset 1.55
+// -> 1.48 ms, smart moves on 4.2M beads 100 -> 90 us.
+template <int CW, int DM, bool CPL, int TIL, class Bead>
+__device__ __forceinline__ void sweep_tile(ArgPtr a, SysPtr S, const Tile &T, int wave, uint64_t s, uint32_t *list,
+                                           uint8_t *tab, const Bead b0, const Bead b1, uint32_t clog,
+                                           unsigned long long acc_prev = 0ull)
+{
+    constexpr bool BT = TIL == TIL_BLOCK;
+    const uint32_t sys = T.sys;
     const SysView v = make_view(S);
-    const FieldCoef fc{S.cAA, S.cAB, S.cBA, S.cBB, S.c0};
-    const bool frozen = S.frozen != 0;
-    const int64_t cell_off = S.cell_off;
-    const int N = S.N, P = S.P;
-    const StreamLane L = stream_lane(T, S, (int)(threadIdx.x & 63));
+    const TileLane L = lane_of<TIL>(T);
     const bool valid = L.valid, own = L.own;
-    const int p = L.p;
+    const int N = S->N, p = L.p;
     const int i0 = 2 * p, i1 = 2 * p + 1;
     const bool has1 = valid && i1 < N;
-    const int64_t slot = S.slot_off + (int64_t)(valid ? L.chain : 0) * (2 * P) + 2 * p;
-    const PosArrays A{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2};
-    const Bead ob0 = b0, ob1 = b1;
 
-    const int cls = chain_cls<false>(S, a.chain_class, clog);
-    int t0, t1;
-    pattern_pair(S, cls, i0, t0, t1);
-    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-    const float delta_s = S.delta * 0x1p-23f;
-    const Draw d0 = move_draw((uint32_t)i0, clog, (uint32_t)s, S.sys_id, k0, k1, delta_s);
-    const Draw d1 = move_draw((uint32_t)i1, clog, (uint32_t)s, S.sys_id, k0, k1, delta_s);
-    bool bad = false;
-    const CellPos c0 = locate(b0, v, bad);
-    const CellPos c1 = locate(b1, v, bad);
-    const int old0 = lin(c0, v), old1 = lin(c1, v);
+    // the logical chain id keys the random numbers and picks the species, so
+    // results do not depend on where a chain sits in memory
+    const int cls = chain_cls<CPL>(S, a->chain_class, clog);
+    const uint32_t pat = pattern_bits(S, cls, i0);
+    const uint32_t k0 = (uint32_t)a->seed, k1 = (uint32_t)(a->seed >> 32);
+    const float delta_s = S->delta * 0x1p-23f;
+    const Draw d0 = move_draw((uint32_t)i0, clog, (uint32_t)s, S->sys_id, k0, k1, delta_s);
+    const Draw d1 = move_draw((uint32_t)i1, clog, (uint32_t)s, S->sys_id, k0, k1, delta_s);
+
+    // Both trial positions are known before either pass (the odd bead's
+    // proposal does not depend on the even pass), so the fields of all four
+    // cells are gathered together: one memory latency instead of two.
     const Bead n0 = propose(b0, d0, v);
     const Bead n1 = propose(b1, d1, v);
-    const CellPos s0 = step(c0, b0, n0, v), s1 = step(c1, b1, n1, v);
-    const int nc0 = lin(s0, v), nc1 = lin(s1, v);
-    const bool g0 = valid && nc0 != old0, g1 = has1 && nc1 != old1;
-    float dw0 = 0.0f, dw1 = 0.0f;
-    if (frozen) {
-        float2 wn0{0.f, 0.f}, wo0{0.f, 0.f}, wn1{0.f, 0.f}, wo1{0.f, 0.f};
-        if (g0) { wn0 = a.omega[cell_off + nc0]; wo0 = a.omega[cell_off + old0]; }
-        if (g1) { wn1 = a.omega[cell_off + nc1]; wo1 = a.omega[cell_off + old1]; }
-        dw0 = t0 ? wn0.y - wo0.y : wn0.x - wo0.x;
-        dw1 = t1 ? wn1.y - wo1.y : wn1.x - wo1.x;
-    } else {
-        RawCount rn0{0u, 0u, 0u, 0u}, ro0{0u, 0u, 0u, 0u}, rn1{0u, 0u, 0u, 0u}, ro1{0u, 0u, 0u, 0u};
-        if (g0) {
-            rn0 = load_raw<CW, DM == 1>(cin, dprev, cell_off + nc0);
-            ro0 = load_raw<CW, DM == 1>(cin, dprev, cell_off + old0);
-        }
-        if (g1) {
-            rn1 = load_raw<CW, DM == 1>(cin, dprev, cell_off + nc1);
-            ro1 = load_raw<CW, DM == 1>(cin, dprev, cell_off + old1);
-        }
-        if (g0) dw0 = omega_of(fc, counts_of<CW>(rn0), t0) - omega_of(fc, counts_of<CW>(ro0), t0);
-        if (g1) dw1 = omega_of(fc, counts_of<CW>(rn1), t1) - omega_of(fc, counts_of<CW>(ro1), t1);
+    CellPos c[4];
+    {
+        const Bead all[4] = {b0, b1, n0, n1};
+        cells_of<2>(all, v, S, own, a->status, c);
     }
-    const float kh = S.k_half;
+    const int t[2] = {(int)(pat & 1u), (int)((pat >> 1) & 1u)};
+    const int oc[2] = {lin(c[0], v), lin(c[1], v)}, nc[2] = {lin(c[2], v), lin(c[3], v)};
+    const ArgPtr ag = later(a);
+    const SysPtr Sg = later(S);
+    // walls: a trial position outside the slab is rejected (and needs no field)
+    const bool out0 = CPL && outside_walls(Sg, c[2].uz), out1 = CPL && outside_walls(Sg, c[3].uz);
+    const bool g[2] = {valid && nc[0] != oc[0] && !out0, has1 && nc[1] != oc[1] && !out1};
+    float dw[2];
+    field_steps<CW, DM, CPL>(ag, Sg, s, nc, oc, t, g, dw);
+    const float kh = Sg->k_half;
     const float3 zero = make_float3(0.0f, 0.0f, 0.0f);
 
-    // even pass: bead 2p, neighbours 2p-1 (previous lane) and 2p+1
+    // even pass: bead 2p, neighbours 2p-1 (previous lane's odd bead) and 2p+1.
+    // dE_b = (k/2) sum_j [2 d.(r - r_j) + |d|^2] = (k/2) [2 d.sum_j (r - r_j) + n_j |d|^2]
     bool acc0;
     {
-        const Bead left = left_neighbour<false>(b1);
+        const Bead left = left_neighbour<BT>(b1);
         const float3 de = bond(n0, b0, v);
         const float3 bl = p > 0 ? bond(b0, left, v) : zero, br = i1 < N ? bond(b0, b1, v) : zero;
         const float nj = (p > 0 ? 1.0f : 0.0f) + (i1 < N ? 1.0f : 0.0f);
-        const float dE = fmaf(fmaf(2.0f, dot3(de, add3(bl, br)), nj * dot3(de, de)), kh, dw0);
-        acc0 = valid && (d0.u < __expf(-dE));
-        if (acc0) b0 = n0;
+        const float dE = fmaf(fmaf(2.0f, dot3(de, add3(bl, br)), nj * dot3(de, de)), kh, dw[0]);
+        acc0 = valid && !out0 && (d0.u < __expf(-dE));
     }
+    const Bead e0 = pick(acc0, n0, b0);
     // odd pass: bead 2p+1, neighbours 2p (this lane, updated) and 2p+2 (next lane)
     bool acc1;
     {
-        const Bead right = right_neighbour<false>(b0);
+        const Bead right = right_neighbour<BT>(e0);
         const float3 de = bond(n1, b1, v);
         const float3 br = i1 + 1 < N ? bond(b1, right, v) : zero;
         const float nj = i1 + 1 < N ? 2.0f : 1.0f;
-        const float dE = fmaf(fmaf(2.0f, dot3(de, add3(bond(b1, b0, v), br)), nj * dot3(de, de)), kh, dw1);
-        acc1 = has1 && (d1.u < __expf(-dE));
-        if (acc1) b1 = n1;
+        const float dE = fmaf(fmaf(2.0f, dot3(de, add3(bond(b1, e0, v), br)), nj * dot3(de, de)), kh, dw[1]);
+        acc1 = has1 && !out1 && (d1.u < __expf(-dE));
+    }
+    const Bead e1 = pick(acc1, n1, b1);
+    const ArgPtr as = later(a);
+    const SysPtr Ss = later(S);
+    const uint32_t lane = (uint32_t)tile_lane<TIL>();
+    store_moved(pos_arrays(as), T.slot, lane * 8u, e0, e1, b0, b1, own && (acc0 || acc1));
+    if constexpr (TIL == TIL_STREAM) {
+        // the end lanes' pairs for the overlap lanes of the next sweep
+        if (own && (lane == 1 || lane == (uint32_t)kStreamLanes))
+            halo_put(as->halo + halo_index((int)((s + 1) & 1), 0, wave, 0, as->halo_cap), lane == 1 ? 0u : kHaloSide, e0,
+                     e1);
+    }
+    // final cells: without coupling a change implies an accepted move, so the
+    // trial cells serve (and the selection costs no registers)
+    const CellPos f0 = CPL ? (acc0 ? c[2] : c[0]) : c[2], f1 = CPL ? (acc1 ? c[3] : c[1]) : c[3];
+    int u0 = t[0], u1 = t[1];
+    if (CPL && !BT && Ss->zones) {   // (the host never packs contexts with zones)
+        const int ncls = zone_convert(as, Ss, sys, clog, cls, valid, p, has1, f0.uz, f1.uz);
+        const uint32_t np = pattern_bits(Ss, ncls, i0);
+        u0 = (int)(np & 1u);
+        u1 = (int)((np >> 1) & 1u);
     }
     const bool own1 = own && has1;
-    if (own) store_moved(A, slot, b0, b1, ob0, ob1, acc0 || acc1);
-    // the end lanes' pairs for the overlap lanes of the next sweep
-    const int lane = (int)(threadIdx.x & 63);
-    if (own && (lane == 1 || lane == kStreamLanes))
-        halo_put(a.halo, (int)((s + 1) & 1), wave, lane == 1 ? 0 : 1, a.halo_cap, b0, b1);
-    tile_finish<CW, DM>(a, wave, sys, cell_off, v, dcur, list, tab, own && acc0 && nc0 != old0, c0, s0, t0,
-                        t0, own1 && acc1 && nc1 != old1, c1, s1, t1, t1, own && acc0, own1 && acc1, own && bad, acc_prev);
+    tile_finish<CW, DM>(as, Ss, BT ? wave * 16 + (int)(threadIdx.x >> 6) : wave, sys, s, v, list, tab,
+                        own && ((acc0 && nc[0] != oc[0]) || (CPL && u0 != t[0])), c[0], f0, t[0], u0,
+                        own1 && ((acc1 && nc[1] != oc[1]) || (CPL && u1 != t[1])), c[1], f1, t[1], u1, own && acc0,
+                        own1 && acc1, acc_prev);
 }
 
 // Fill halo buffer a.buf from the position arrays: one thread per stream
@@ -1214,13 +1208,11 @@ __global__ __launch_bounds__(256) void k_stream_halo(HaloArgs a)
     const int64_t tile = i >> 1;
     const int side = (int)(i & 1);
     const Tile T = a.ptiles[tile];
-    const DevSys &S = a.systems[stile_sys(T)];
-    const StreamLane L = stream_lane(T, S, side == 0 ? 1 : kStreamLanes);
-    if (!L.own) return;
+    const int lane = side == 0 ? 1 : kStreamLanes;
+    if (lane >= (int)(T.lanes & 2047u)) return;
     Bead b0, b1;
-    load_pair(PosArrays{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2}, S.slot_off + (int64_t)L.chain * (2 * S.P) + 2 * L.p,
-              b0, b1);
-    halo_put(a.halo, a.buf, tile, side, a.halo_cap, b0, b1);
+    load_pair(pos_arrays(a), T.slot + 2 * lane, 0u, b0, b1);
+    halo_put(a.halo + halo_index(a.buf, 0, tile, side, a.halo_cap), 0u, b0, b1);
 }
 
 // ---------------------------------------------------------------------------
@@ -1264,7 +1256,7 @@ __device__ __forceinline__ double3 pos64(const BeadCell &a, const SysView &v)
 // below 0.99 cell edges; F gets the bond force at b (FP64).
 template <class Bead>
 __device__ __forceinline__ Bead smc_propose(const Bead &b, const Bead &nl, bool hl, const Bead &nr, bool hr,
-                                            const DevSys &S, const SysView &v, const double xi[3], double3 &F,
+                                            SysPtr S, const SysView &v, const double xi[3], double3 &F,
                                             bool &inside)
 {
     const double3 r = pos64(b, v);
@@ -1277,121 +1269,89 @@ __device__ __forceinline__ Bead smc_propose(const Bead &b, const Bead &nl, bool 
         const double3 q = pos64(nr, v);
         fx += q.x - r.x; fy += q.y - r.y; fz += q.z - r.z;
     }
-    F = make_double3(S.k_spring * fx, S.k_spring * fy, S.k_spring * fz);
+    F = make_double3(S->k_spring * fx, S->k_spring * fy, S->k_spring * fz);
     Draw d;
-    d.dx = (float)(S.smc_A * F.x + S.smc_s2A * xi[0]);
-    d.dy = (float)(S.smc_A * F.y + S.smc_s2A * xi[1]);
-    d.dz = (float)(S.smc_A * F.z + S.smc_s2A * xi[2]);
+    d.dx = (float)(S->smc_A * F.x + S->smc_s2A * xi[0]);
+    d.dy = (float)(S->smc_A * F.y + S->smc_s2A * xi[1]);
+    d.dz = (float)(S->smc_A * F.z + S->smc_s2A * xi[2]);
     d.u = 0.0f;
     // a displacement of 0.99 cell edges or more is rejected: the condition is
     // symmetric in r and r', so detailed balance holds, and a kept trial move
     // changes each cell index by at most one
-    inside = fabsf(d.dx) < S.dmax[0] && fabsf(d.dy) < S.dmax[1] && fabsf(d.dz) < S.dmax[2];
+    inside = fabsf(d.dx) < S->dmax[0] && fabsf(d.dy) < S->dmax[1] && fabsf(d.dz) < S->dmax[2];
     if (!inside) d.dx = d.dy = d.dz = 0.0f;
     return propose(b, d, v);
 }
 
 // log of q(r'->r) / q(r->r') for q(r->r') ~ exp(-|r'-r-A F(r)|^2 / (4A)),
 // with de the stored displacement and F(r') = F(r) - k n_nb de (FP32).
-__device__ __forceinline__ float smc_log_ratio(const DevSys &S, float3 de, double3 F, int n_nb)
+__device__ __forceinline__ float smc_log_ratio(SysPtr S, float3 de, double3 F, int n_nb)
 {
-    const float A = S.smc_Af, kn = S.k_f * (float)n_nb;
+    const float A = S->smc_Af, kn = S->k_f * (float)n_nb;
     const float fx = (float)F.x, fy = (float)F.y, fz = (float)F.z;
     const float3 f = make_float3(de.x - A * fx, de.y - A * fy, de.z - A * fz);
     const float3 r = make_float3(de.x + A * (fx - kn * de.x), de.y + A * (fy - kn * de.y), de.z + A * (fz - kn * de.z));
-    return (dot3(f, f) - dot3(r, r)) * S.smc_inv4A;
-}
-
-// Field difference between a trial cell and the old cell of one bead.
-template <int CW, int DM>
-__device__ __forceinline__ float field_step(const SweepArgs &a, bool frozen, const FieldCoef &fc,
-                                            const uint32_t *cin, const uint32_t *dprev, int64_t cell_off,
-                                            int nc, int old, int t, bool gather, bool umb, float umb_coef)
-{
-    float dw = 0.0f;
-    if (frozen) {
-        float2 wn{0.f, 0.f}, wo{0.f, 0.f};
-        if (gather) { wn = a.omega[cell_off + nc]; wo = a.omega[cell_off + old]; }
-        dw = t ? wn.y - wo.y : wn.x - wo.x;
-    } else {
-        RawCount rn{0u, 0u, 0u, 0u}, ro{0u, 0u, 0u, 0u};
-        if (gather) {
-            rn = load_raw<CW, DM == 1>(cin, dprev, cell_off + nc);
-            ro = load_raw<CW, DM == 1>(cin, dprev, cell_off + old);
-            float2 un{0.f, 0.f}, uo{0.f, 0.f};
-            if (umb) { un = a.tgt[cell_off + nc]; uo = a.tgt[cell_off + old]; }
-            dw = omega_of(fc, counts_of<CW>(rn), t) - omega_of(fc, counts_of<CW>(ro), t);
-            if (umb) dw += umb_step(umb_coef, un, uo, t);
-        }
-    }
-    return dw;
+    return (dot3(f, f) - dot3(r, r)) * S->smc_inv4A;
 }
 
 // One wave tile with smart moves.  The odd bead's proposal depends on the
 // even pass (its bond force uses the moved even beads), so the two passes
 // gather their fields one after the other.
-template <int R, int CW, int DM, bool CPL, bool BT, class Bead>
-__device__ __forceinline__ void sweep_tile_smc(const SweepArgs &a, int wave, uint64_t s, const uint32_t *cin,
-                                               const uint32_t *dprev, uint32_t *dcur, uint32_t *list,
-                                               uint8_t *tab, Bead b0, Bead b1, uint32_t clog)
+template <int CW, int DM, bool CPL, int TIL, class Bead>
+__device__ __forceinline__ void sweep_tile_smc(ArgPtr a, SysPtr S, const Tile &T, int wave, uint64_t s,
+                                               uint32_t *list, uint8_t *tab, const Bead b0, const Bead b1,
+                                               uint32_t clog)
 {
-    const Tile T = tile_table<BT>(a)[wave];
-    const DevSys &S = a.systems[T.sys];
+    constexpr bool BT = TIL == TIL_BLOCK;
     const SysView v = make_view(S);
-    const FieldCoef fc{S.cAA, S.cAB, S.cBA, S.cBB, S.c0};
-    const bool frozen = S.frozen != 0;
-    const int64_t cell_off = S.cell_off;
-    const int N = S.N, P = S.P;
-    const int lane = tile_lane<BT>();
-    const int g = (int)(((float)lane + 0.5f) * S.inv_P);
-    const int p = lane - g * P;
-    const int nin = min(tile_capacity<BT>(S), S.n_chains - (int)T.chain0);
-    const bool active = g < nin;
-    const int chain = (int)T.chain0 + (active ? g : 0);
+    const TileLane L = lane_of<TIL>(T);
+    const bool active = L.valid;
+    const int N = S->N, p = L.p;
     const int i0 = 2 * p, i1 = 2 * p + 1;
     const bool has1 = active && i1 < N;
-    const int64_t slot = S.slot_off + (int64_t)chain * (2 * P) + i0;
-    const PosArrays A{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2};
-    const Bead ob0 = b0, ob1 = b1;   // the stored state, to write back only what changes
-    const int cls = chain_cls<CPL>(S, a.chain_class, clog);
-    const int t0 = pattern_type(S, cls, i0);
-    const int t1 = pattern_type(S, cls, i1 < N ? i1 : i0);
-    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-    const float kh = S.k_half;
-    const bool umb = CPL && S.umb != 0;
-    const float umb_coef = S.umb_coef;
-    bool bad = false;
-    const CellPos c0 = locate(b0, v, bad);
-    const CellPos c1 = locate(b1, v, bad);
-    const int old0 = lin(c0, v);
-    const int old1 = lin(c1, v);
+    const int cls = chain_cls<CPL>(S, a->chain_class, clog);
+    const uint32_t pat = pattern_bits(S, cls, i0);
+    const int t0 = (int)(pat & 1u), t1 = (int)((pat >> 1) & 1u);
+    const uint32_t k0 = (uint32_t)a->seed, k1 = (uint32_t)(a->seed >> 32);
+    const float kh = S->k_half;
+    CellPos c[2];
+    {
+        const Bead all[2] = {b0, b1};
+        cells_of<2>(all, v, S, active, a->status, c);
+    }
+    const int old0 = lin(c[0], v), old1 = lin(c[1], v);
 
     // even pass: bead 2p, neighbours 2p-1 (previous lane's odd bead) and 2p+1
     bool acc0;
+    Bead e0, e1;   // the pair after its moves
     int nc0;
     CellPos s0;
     {
         double xi[3];
         float u;
-        smc_draw((uint32_t)i0, clog, (uint32_t)s, S.sys_id, k0, k1, xi, u);
+        smc_draw((uint32_t)i0, clog, (uint32_t)s, S->sys_id, k0, k1, xi, u);
         const Bead left = left_neighbour<BT>(b1);
         const bool hl = p > 0, hr = i1 < N;
         double3 F;
         bool inside;
-        const Bead n0 = smc_propose(b0, left, hl, b1, hr, S, v, xi, F, inside);
-        s0 = step(c0, b0, n0, v);
+        const Bead trial[1] = {smc_propose(b0, left, hl, b1, hr, S, v, xi, F, inside)};
+        CellPos tc[1];
+        cells_of<0>(trial, v, S, false, a->status, tc);
+        s0 = tc[0];
         nc0 = lin(s0, v);
-        if (CPL) inside = inside && !outside_walls(S, zcell(s0, n0));
-        const float dw = field_step<CW, DM>(a, frozen, fc, cin, dprev, cell_off, nc0, old0, t0,
-                                            active && inside && nc0 != old0, umb, umb_coef);
-        const float3 de = bond(n0, b0, v);
+        if (CPL) inside = inside && !outside_walls(S, s0.uz);
+        const int nc[1] = {nc0}, oc[1] = {old0}, t[1] = {t0};
+        const bool g[1] = {active && inside && nc0 != old0};
+        float dw[1];
+        field_steps<CW, DM, CPL>(a, S, s, nc, oc, t, g, dw);
+        const float3 de = bond(trial[0], b0, v);
         const float dd = dot3(de, de);
         float dE = 0.0f;
         if (hl) dE += 2.0f * dot3(de, bond(b0, left, v)) + dd;
         if (hr) dE += 2.0f * dot3(de, bond(b0, b1, v)) + dd;
-        dE = dE * kh + dw - smc_log_ratio(S, de, F, (hl ? 1 : 0) + (hr ? 1 : 0));
+        dE = dE * kh + dw[0] - smc_log_ratio(S, de, F, (hl ? 1 : 0) + (hr ? 1 : 0));
         acc0 = active && inside && (u < __expf(-dE));
-        if (acc0) b0 = n0;
+        e0 = pick(acc0, trial[0], b0);
     }
     // odd pass: bead 2p+1, neighbours 2p (this lane, moved) and 2p+2 (next lane)
     bool acc1;
@@ -1400,38 +1360,44 @@ __device__ __forceinline__ void sweep_tile_smc(const SweepArgs &a, int wave, uin
     {
         double xi[3];
         float u;
-        smc_draw((uint32_t)i1, clog, (uint32_t)s, S.sys_id, k0, k1, xi, u);
-        const Bead right = right_neighbour<BT>(b0);
+        smc_draw((uint32_t)i1, clog, (uint32_t)s, S->sys_id, k0, k1, xi, u);
+        const Bead right = right_neighbour<BT>(e0);
         const bool hr = i1 + 1 < N;
         double3 F;
         bool inside;
-        const Bead n1 = smc_propose(b1, b0, true, right, hr, S, v, xi, F, inside);
-        s1 = step(c1, b1, n1, v);
+        const Bead trial[1] = {smc_propose(b1, e0, true, right, hr, S, v, xi, F, inside)};
+        CellPos tc[1];
+        cells_of<0>(trial, v, S, false, a->status, tc);
+        s1 = tc[0];
         nc1 = lin(s1, v);
-        if (CPL) inside = inside && !outside_walls(S, zcell(s1, n1));
-        const float dw = field_step<CW, DM>(a, frozen, fc, cin, dprev, cell_off, nc1, old1, t1,
-                                            has1 && inside && nc1 != old1, umb, umb_coef);
-        const float3 de = bond(n1, b1, v);
+        if (CPL) inside = inside && !outside_walls(S, s1.uz);
+        const int nc[1] = {nc1}, oc[1] = {old1}, t[1] = {t1};
+        const bool g[1] = {has1 && inside && nc1 != old1};
+        float dw[1];
+        field_steps<CW, DM, CPL>(a, S, s, nc, oc, t, g, dw);
+        const float3 de = bond(trial[0], b1, v);
         const float dd = dot3(de, de);
-        float dE = 2.0f * dot3(de, bond(b1, b0, v)) + dd;
+        float dE = 2.0f * dot3(de, bond(b1, e0, v)) + dd;
         if (hr) dE += 2.0f * dot3(de, bond(b1, right, v)) + dd;
-        dE = dE * kh + dw - smc_log_ratio(S, de, F, 1 + (hr ? 1 : 0));
+        dE = dE * kh + dw[0] - smc_log_ratio(S, de, F, 1 + (hr ? 1 : 0));
         acc1 = has1 && inside && (u < __expf(-dE));
-        if (acc1) b1 = n1;
+        e1 = pick(acc1, trial[0], b1);
     }
-    if (active) store_moved(A, slot, b0, b1, ob0, ob1, acc0 || acc1);
+    store_moved(pos_arrays(a), T.slot, (uint32_t)tile_lane<TIL>() * 8u, e0, e1, b0, b1,
+                active && (acc0 || acc1));
     // final cells: without coupling a change implies an accepted move, so the
     // trial cells serve (and the selection costs no registers)
-    const CellPos f0 = CPL ? (acc0 ? s0 : c0) : s0, f1 = CPL ? (acc1 ? s1 : c1) : s1;
+    const CellPos f0 = CPL ? (acc0 ? s0 : c[0]) : s0, f1 = CPL ? (acc1 ? s1 : c[1]) : s1;
     int u0 = t0, u1 = t1;
-    if (CPL && !BT && S.zones) {   // (the host never packs contexts with zones)
-        const int ncls = zone_convert(a, S, T.sys, clog, cls, active, p, P, has1, zcell(f0, b0), zcell(f1, b1));
-        u0 = pattern_type(S, ncls, i0);
-        u1 = pattern_type(S, ncls, i1 < N ? i1 : i0);
+    if (CPL && !BT && S->zones) {   // (the host never packs contexts with zones)
+        const int ncls = zone_convert(a, S, T.sys, clog, cls, active, p, has1, f0.uz, f1.uz);
+        const uint32_t np = pattern_bits(S, ncls, i0);
+        u0 = (int)(np & 1u);
+        u1 = (int)((np >> 1) & 1u);
     }
-    tile_finish<CW, DM>(a, BT ? wave * 16 + (int)(threadIdx.x >> 6) : wave, T.sys, cell_off, v, dcur, list, tab,
-                        active && ((acc0 && nc0 != old0) || u0 != t0), c0, f0, t0, u0,
-                        has1 && ((acc1 && nc1 != old1) || u1 != t1), c1, f1, t1, u1, acc0, acc1, active && bad, 0ull);
+    tile_finish<CW, DM>(a, S, BT ? wave * 16 + (int)(threadIdx.x >> 6) : wave, T.sys, s, v, list, tab,
+                        active && ((acc0 && nc0 != old0) || u0 != t0), c[0], f0, t0, u0,
+                        has1 && ((acc1 && nc1 != old1) || u1 != t1), c[1], f1, t1, u1, acc0, acc1, 0ull);
 }
 
 // The sweep kernel: one launch per sweep for every system.  With one tile
@@ -1442,30 +1408,33 @@ __device__ __forceinline__ void sweep_tile_smc(const SweepArgs &a, int wave, uin
 // one-tile case.  With FI every thread also folds count words of the
 // previous sweep: the first word's loads are issued before the move work
 // and its stores after it, so they overlap.
-template <int R, int CW, bool LOOP, int DM, bool SMC, bool CPL, bool BT, bool ST = false>
-__device__ __forceinline__ void sweep_body(const SweepArgs &a)
+template <int R, int CW, bool LOOP, int DM, bool SMC, bool CPL, int TIL>
+__device__ __forceinline__ void sweep_body(ArgPtr a)
 {
     using Bead = typename std::conditional<R == REPR_F32, BeadF32, BeadCell>::type;
     constexpr bool FI = DM == 1;
-    constexpr int CAP = DM == 2 ? kListFaces : kListCells;
-    const uint64_t s = *a.sweep_ctr + a.rel;
-    const int64_t W = a.count_words;
-    // mode 1: counts of sweep s are B[s-1] + D[s-1]; this sweep adds to D[s],
-    // writes B[s] and clears D[s+1] (last read by sweep s-1).  Mode 2: the
-    // face fluxes of sweep s go to flux buffer s mod 2 (three W-word arrays).
-    // Mode 3: the counts are B[s mod 2]; the changes go straight into its
-    // mirror B[(s+1) mod 2], which holds the same counts when the sweep
-    // starts and is read by no gather of this sweep.
-    const uint32_t *cin = FI ? a.base + ((s + 1) & 1) * W : (DM == 3 ? a.base + (s & 1) * W : a.base);
-    const uint32_t *dprev = FI ? a.delta + ((s + 2) % 3) * W : nullptr;
-    uint32_t *dcur = FI ? a.delta + (s % 3) * W
-                        : (DM == 2 ? a.flux + (s & 1) * 3 * W : (DM == 3 ? a.base + ((s + 1) & 1) * W : a.delta));
-    const int wave = BT ? block_tile(a.xcd_remap) : wave_tile(a.waves_per_block, a.xcd_remap);
+    const Head h = head_of(a, R == REPR_CELL);
+    // (wave-uniform; readfirstlane lets the tables be read with scalar loads)
+    const int bid = block_index(h.remap);
+    const int wave = __builtin_amdgcn_readfirstlane(
+        TIL == TIL_BLOCK ? bid : bid * h.waves_per_block + (int)(threadIdx.x >> 6));
+    const bool mine = wave < h.n_tiles;
+    // the tile, the sweep counter and the tile's acceptance count (see
+    // counts_per_tile; acc_tile is null for the other kernels) together
+    Tile T = tile_at(h.tiles, mine ? wave : 0);
+    uint64_t s = *(const SOMA_CONST uint64_t *)(uintptr_t)h.ctr;
+    const bool per_tile = !LOOP && TIL != TIL_BLOCK && h.acc_tile != nullptr && mine;
+    unsigned long long accp = *(const SOMA_CONST unsigned long long *)(per_tile ? (uintptr_t)(h.acc_tile + wave) : (uintptr_t)h.ctr);
+    asm volatile("" : "+s"(T.sys), "+s"(T.chain0), "+s"(T.slot), "+s"(T.chain), "+s"(T.lanes), "+s"(T.inv_P), "+s"(s),
+                      "+s"(accp));
+    s += h.rel;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     // this wave's list of density changes and its merge table
     HIP_DYNAMIC_SHARED(uint32_t, agg_lds)
-    uint32_t *list = agg_lds + (threadIdx.x >> 6) * list_words(CAP);
-    uint8_t *tab = reinterpret_cast<uint8_t *>(list + 2 * CAP);
+    uint32_t *list = agg_lds + (threadIdx.x >> 6) * list_words(DM == 2);
+    uint8_t *tab = reinterpret_cast<uint8_t *>(list + list_words(DM == 2) - kMergeTab / 4);
+    const int64_t W = FI || DM == 2 ? a->count_words : 0;
+    const uint32_t *cin = FI ? counts_in<DM>(a, s) : nullptr, *dprev = FI ? delta_in<DM>(a, s) : nullptr;
     uint32_t fb = 0u, fd = 0u;
     if constexpr (FI) {
         if (gtid < W) {
@@ -1480,46 +1449,42 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         // pipeline: the positions of a wave's next tile are loaded before
         // the current tile's field gathers, so their latency overlaps the
         // current tile's work.
-        const int n_waves = (int)gridDim.x * a.waves_per_block;
+        const int n_waves = (int)gridDim.x * h.waves_per_block;
         Bead nb0, nb1;
         uint32_t nclog = 0u;
-        if (wave < a.n_tiles) tile_load<false>(a, wave, nb0, nb1, nclog);
-        for (int t = wave; t < a.n_tiles; t += n_waves) {
+        Tile NT = T;
+        if (mine) tile_load<TIL>(a, h, NT, wave, s, nb0, nb1, nclog);
+        for (int t = wave; t < h.n_tiles; t += n_waves) {
             const Bead b0 = nb0, b1 = nb1;
             const uint32_t clog = nclog;
-            if (t + n_waves < a.n_tiles) tile_load<false>(a, t + n_waves, nb0, nb1, nclog);
-            if (SMC && a.systems[a.tiles[t].sys].smc)
-                sweep_tile_smc<R, CW, DM, CPL, false>(a, t, s, cin, dprev, dcur, list, tab, b0, b1, clog);
+            const Tile C = NT;
+            if (t + n_waves < h.n_tiles) {
+                NT = tile_at(h.tiles, t + n_waves);
+                tile_load<TIL>(a, h, NT, t + n_waves, s, nb0, nb1, nclog);
+            }
+            const SysPtr S = sys_at(h.systems, C.sys);
+            if (SMC && S->smc)
+                sweep_tile_smc<CW, DM, CPL, TIL>(a, S, C, t, s, list, tab, b0, b1, clog);
             else
-                sweep_tile<R, CW, DM, CPL, false>(a, t, s, cin, dprev, dcur, list, tab, b0, b1, clog);
+                sweep_tile<CW, DM, CPL, TIL>(a, S, C, t, s, list, tab, b0, b1, clog);
         }
     } else {
         // block tiles: the test is uniform over the block, so every thread
         // of a working block reaches the barriers of the tile
-        // the tile's acceptance count is read with its positions (see
-        // counts_per_tile; a.acc_tile is null for the other kernels)
-        if constexpr (ST) {
-            if (wave < a.n_ptiles) {
-                Bead b0, b1;
-                uint32_t clog;
-                stream_load(a, wave, s, b0, b1, clog);
-                const unsigned long long accp = a.acc_tile ? a.acc_tile[wave] : 0ull;
-                    sweep_tile_stream<R, CW, DM>(a, wave, s, cin, dprev, dcur, list, tab, b0, b1, clog, accp);
-            }
-        } else if (wave < (BT ? a.n_ptiles : a.n_tiles)) {
+        if (mine) {
             Bead b0, b1;
             uint32_t clog;
-            tile_load<BT>(a, wave, b0, b1, clog);
-            const unsigned long long accp = !BT && a.acc_tile ? a.acc_tile[wave] : 0ull;
-            if (SMC && a.systems[tile_table<BT>(a)[wave].sys].smc)
-                sweep_tile_smc<R, CW, DM, CPL, BT>(a, wave, s, cin, dprev, dcur, list, tab, b0, b1, clog);
+            tile_load<TIL>(a, h, T, wave, s, b0, b1, clog);
+            const SysPtr S = sys_at(h.systems, T.sys);
+            if (SMC && S->smc)
+                sweep_tile_smc<CW, DM, CPL, TIL>(a, S, T, wave, s, list, tab, b0, b1, clog);
             else
-                sweep_tile<R, CW, DM, CPL, BT>(a, wave, s, cin, dprev, dcur, list, tab, b0, b1, clog, accp);
+                sweep_tile<CW, DM, CPL, TIL>(a, S, T, wave, s, list, tab, b0, b1, clog, accp);
         }
     }
     if constexpr (FI) {
-        uint32_t *bcur = a.base + (s & 1) * W;
-        uint32_t *dnext = a.delta + ((s + 1) % 3) * W;
+        uint32_t *bcur = a->base + (s & 1) * W;
+        uint32_t *dnext = a->delta + ((s + 1) % 3) * W;
         const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
         bool ovf = false;
         if (gtid < W) {
@@ -1534,38 +1499,39 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             bcur[i] = w;
             dnext[i] = 0u;
         }
-        if (ovf) atomicOr(a.status, ST_COUNT_OVERFLOW);
+        if (ovf) atomicOr(a->status, ST_COUNT_OVERFLOW);
     }
     if constexpr (DM == 2) {
         // clear the flux buffer of sweep s + 1 (folded after sweep s - 1);
         // its 3 W words are a multiple of 4 and 16-byte aligned
-        uint4 *fn = reinterpret_cast<uint4 *>(a.flux + ((s + 1) & 1) * 3 * W);
+        uint4 *fn = reinterpret_cast<uint4 *>(a->flux + ((s + 1) & 1) * 3 * W);
         const int64_t n4 = 3 * W / 4, nthreads = (int64_t)gridDim.x * blockDim.x;
         for (int64_t i = gtid; i < n4; i += nthreads) fn[i] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
 
+// (the body reads the arguments through the kernel argument segment, see
+// `later`; they are the first and only explicit argument)
 template <int R, int CW, bool LOOP, int DM, bool SMC, bool CPL, bool BT>
-__global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
+__global__ __launch_bounds__(1024) void k_sweep(SweepArgs)
 {
-    sweep_body<R, CW, LOOP, DM, SMC, CPL, BT>(a);
+    sweep_body<R, CW, LOOP, DM, SMC, CPL, BT ? TIL_BLOCK : TIL_WAVE>((ArgPtr)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // The plain one-tile-per-wave sweep (uniform moves, no coupling) fits in 64
-// VGPRs: it asks for eight waves per SIMD, the most a SIMD holds (the SGPRs
-// beyond that budget live in VGPR lanes).  The sweep waits on memory, and
-// the eighth wave hides enough of it to pay for those moves.
+// VGPRs: it asks for eight waves per SIMD, the most a SIMD holds (see
+// `later` for the SGPRs).
 template <int R, int CW, int DM>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_plain(SweepArgs a)
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_plain(SweepArgs)
 {
-    sweep_body<R, CW, false, DM, false, false, false, false>(a);
+    sweep_body<R, CW, false, DM, false, false, TIL_WAVE>((ArgPtr)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // Stream tiles, with the same register budget.
 template <int R, int CW, int DM>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_stream(SweepArgs a)
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_stream(SweepArgs)
 {
-    sweep_body<R, CW, false, DM, false, false, false, true>(a);
+    sweep_body<R, CW, false, DM, false, false, TIL_STREAM>((ArgPtr)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // Density mode 2: counts += divergence of the face fluxes of sweep s, per
@@ -1723,32 +1689,23 @@ __global__ __launch_bounds__(256) void k_density(DensityArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(
         a.tile_begin + (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (wave >= a.tile_end) return;
-    const Tile T = a.tiles[wave];
-    const DevSys &S = a.systems[T.sys];
+    const Tile T = tile_at(a.tiles, wave);
+    const SysPtr S = sys_at(a.systems, T.sys);
     const SysView v = make_view(S);
-    const int N = S.N, P = S.P;
-    const int lane = (int)(threadIdx.x & 63);
-    const int g = (int)(((float)lane + 0.5f) * S.inv_P);
-    const int p = lane - g * P;
-    const int nin = min(S.G, S.n_chains - (int)T.chain0);
-    const bool active = g < nin;
-    if (!active) return;
-    const int chain = (int)T.chain0 + g;
-    const int i0 = 2 * p, i1 = 2 * p + 1;
-    const int64_t slot = S.slot_off + (int64_t)chain * (2 * P) + i0;
-    const PosArrays A{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2};
-    Bead b0, b1;
-    load_pair(A, slot, b0, b1);
-    bool bad = false, ovf = false;
-    const int c0 = cell_of(b0, v, bad);
-    const int cls = chain_cls(S, a.chain_class, a.chain_id[S.chain_off + chain]);
-    ovf |= scatter_count<CW>(a.counts, S.cell_off + c0, pattern_type(S, cls, i0));
-    if (i1 < N) {
-        const int c1 = cell_of(b1, v, bad);
-        ovf |= scatter_count<CW>(a.counts, S.cell_off + c1, pattern_type(S, cls, i1));
-    }
+    const TileLane L = lane_of<TIL_WAVE>(T);
+    if (!L.valid) return;
+    const int i0 = 2 * L.p;
+    const bool has1 = i0 + 1 < S->N;
+    Bead b[2];
+    load_pair(pos_arrays(a), T.slot, (uint32_t)tile_lane<TIL_WAVE>() * 8u, b[0], b[1]);
+    if (!has1) b[1] = b[0];      // (the padding slot of an odd chain)
+    CellPos c[2];
+    cells_of<2>(b, v, S, true, a.status, c);
+    const int cls = chain_cls(S, a.chain_class, a.chain_id[T.chain + L.g]);
+    const uint32_t pat = pattern_bits(S, cls, i0);
+    bool ovf = scatter_count<CW>(a.counts, S->cell_off + lin(c[0], v), (int)(pat & 1u));
+    if (has1) ovf |= scatter_count<CW>(a.counts, S->cell_off + lin(c[1], v), (int)((pat >> 1) & 1u));
     if (ovf) atomicOr(a.status, ST_COUNT_OVERFLOW);
-    if (bad) atomicOr(a.status, ST_CELL_OVERFLOW);
 }
 
 // Fields of one system as float [2][M] (A then B), from its counts or its
@@ -1765,7 +1722,7 @@ __global__ __launch_bounds__(256) void k_fields(FieldArgs a)
         wa = w.x;
         wb = w.y;
     } else {
-        const FieldCoef fc{S.cAA, S.cAB, S.cBA, S.cBB, S.c0};
+        const FieldCoef fc{S.c_same, S.c_other, S.c0};
         const uint2 n = load_counts<CW>(a.counts, S.cell_off + c);
         wa = omega_of(fc, n, 0);
         wb = omega_of(fc, n, 1);
@@ -1812,22 +1769,18 @@ __global__ __launch_bounds__(256) void k_reorder_keys(ReorderArgs a)
     using Bead = typename std::conditional<R == REPR_F32, BeadF32, BeadCell>::type;
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (wave >= a.n_tiles) return;
-    const Tile T = a.tiles[wave];
-    const DevSys &S = a.systems[T.sys];
+    const Tile T = tile_at(a.tiles, wave);
+    const SysPtr S = sys_at(a.systems, T.sys);
     const SysView v = make_view(S);
-    const int P = S.P;
-    const int lane = (int)(threadIdx.x & 63);
-    const int g = (int)(((float)lane + 0.5f) * S.inv_P);
-    const int p = lane - g * P;
-    const int nin = min(S.G, S.n_chains - (int)T.chain0);
-    if (g >= nin || p != 0) return;
-    const int chain = (int)T.chain0 + g;
-    const int64_t slot = S.slot_off + (int64_t)chain * (2 * P);
-    Bead b0, b1;
-    load_pair(PosArrays{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2}, slot, b0, b1);
-    bool bad = false;
-    const uint32_t key = (uint32_t)(S.cell_off + cell_of(b0, v, bad));
-    a.keys[S.chain_off + chain] = key;
+    const TileLane L = lane_of<TIL_WAVE>(T);
+    if (!L.valid || L.p != 0) return;
+    Bead b[2];
+    load_pair(pos_arrays(a), T.slot, (uint32_t)tile_lane<TIL_WAVE>() * 8u, b[0], b[1]);
+    CellPos c[1];
+    const Bead first[1] = {b[0]};
+    cells_of<1>(first, v, S, false, a.status, c);
+    const uint32_t key = (uint32_t)(S->cell_off + lin(c[0], v));
+    a.keys[T.chain + L.g] = key;
     atomicAdd(a.hist + key, 1u);
 }
 
@@ -1914,24 +1867,19 @@ __global__ __launch_bounds__(256) void k_reorder_permute(ReorderArgs a)
     using Bead = typename std::conditional<R == REPR_F32, BeadF32, BeadCell>::type;
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (wave >= a.n_tiles) return;
-    const Tile T = a.tiles[wave];
-    const DevSys &S = a.systems[T.sys];
-    const int P = S.P;
-    const int lane = (int)(threadIdx.x & 63);
-    const int g = (int)(((float)lane + 0.5f) * S.inv_P);
-    const int p = lane - g * P;
-    const int nin = min(S.G, S.n_chains - (int)T.chain0);
-    if (g >= nin) return;
-    const int chain = (int)T.chain0 + g;
-    const int64_t old = (int64_t)a.perm[S.chain_off + chain] - S.chain_off;
-    if (old < 0 || old >= S.n_chains) {           // a chain left its system: never expected
+    const Tile T = tile_at(a.tiles, wave);
+    const SysPtr S = sys_at(a.systems, T.sys);
+    const TileLane L = lane_of<TIL_WAVE>(T);
+    if (!L.valid) return;
+    const int64_t old = (int64_t)a.perm[T.chain + L.g] - S->chain_off;
+    if (old < 0 || old >= S->n_chains) {           // a chain left its system: never expected
         atomicOr(a.status, ST_INTERNAL);
         return;
     }
     Bead b0, b1;
-    load_pair(PosArrays{a.P0, a.P1, a.P2, a.C0, a.C1, a.C2}, S.slot_off + old * (2 * P) + 2 * p, b0, b1);
-    store_pair(PosArrays{a.Q0, a.Q1, a.Q2, a.D0, a.D1, a.D2}, S.slot_off + (int64_t)chain * (2 * P) + 2 * p, b0, b1);
-    if (p == 0) a.chain_id2[S.chain_off + chain] = a.chain_id[S.chain_off + old];
+    load_pair(pos_arrays(a), S->slot_off + old * (2 * S->P) + 2 * L.p, 0u, b0, b1);
+    store_pair(PosArrays{a.Q0, a.Q1, a.Q2, a.D0, a.D1, a.D2}, T.slot, (uint32_t)tile_lane<TIL_WAVE>() * 8u, b0, b1);
+    if (L.p == 0) a.chain_id2[T.chain + L.g] = a.chain_id[S->chain_off + old];
 }
 
 // Logical chain ids in system order (identity within each system).
@@ -1939,11 +1887,9 @@ __global__ __launch_bounds__(256) void k_iota_chains(ReorderArgs a)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     if (wave >= a.n_tiles) return;
-    const Tile T = a.tiles[wave];
-    const DevSys &S = a.systems[T.sys];
-    const int lane = (int)(threadIdx.x & 63);
-    const int chain = (int)T.chain0 + lane;
-    if (lane < S.G && chain < S.n_chains) a.chain_id[S.chain_off + chain] = (uint32_t)chain;
+    const Tile T = tile_at(a.tiles, wave);
+    const TileLane L = lane_of<TIL_WAVE>(T);
+    if (L.valid && L.p == 0) a.chain_id[T.chain + L.g] = (uint32_t)(T.chain0 + L.g);
 }
 
 // ---------------------------------------------------------------------------
@@ -2372,7 +2318,7 @@ template <int R, int CW, int DM, bool SMC>
 static void launch_sweep_d(const SweepArgs &a, int blocks, hipStream_t st)
 {
     const dim3 g(blocks), b(64 * a.waves_per_block);
-    const size_t lds = sizeof(uint32_t) * list_words(DM == 2 ? kListFaces : kListCells) * a.waves_per_block;
+    const size_t lds = sizeof(uint32_t) * list_words(DM == 2) * a.waves_per_block;
     // contexts without walls, zones, umbrella or caller-set classes launch
     // kernels built without that code (fewer registers)
     // block tiles: one tile per block (never with conversion zones, whose
@@ -2380,6 +2326,11 @@ static void launch_sweep_d(const SweepArgs &a, int blocks, hipStream_t st)
     // only the plain and stream kernels count acceptances per tile
     SweepArgs o = a;
     if (!counts_per_tile(a)) o.acc_tile = nullptr;
+    const bool stream = !SMC && !o.cpl && o.max_blocks == 0 && o.packed == 2;
+    const bool block = o.max_blocks == 0 && o.packed == 1;
+    o.wtiles = stream || block ? o.ptiles : o.tiles;
+    o.n_wtiles = stream || block ? o.n_ptiles : o.n_tiles;
+    o.remap_blocks = o.xcd_remap ? blocks & ~7 : 0;
     if (o.cpl) {
         if (o.max_blocks > 0) hipLaunchKernelGGL((k_sweep<R, CW, true, DM, SMC, true, false>), g, b, lds, st, o);
         else if (o.packed == 1) hipLaunchKernelGGL((k_sweep<R, CW, false, DM, SMC, true, true>), g, b, lds, st, o);
@@ -2387,7 +2338,7 @@ static void launch_sweep_d(const SweepArgs &a, int blocks, hipStream_t st)
     } else {
         if (o.max_blocks > 0) hipLaunchKernelGGL((k_sweep<R, CW, true, DM, SMC, false, false>), g, b, lds, st, o);
         else if (o.packed == 1) hipLaunchKernelGGL((k_sweep<R, CW, false, DM, SMC, false, true>), g, b, lds, st, o);
-        else if (!SMC && o.packed == 2) hipLaunchKernelGGL((k_sweep_stream<R, CW, DM>), g, b, lds, st, o);
+        else if (stream) hipLaunchKernelGGL((k_sweep_stream<R, CW, DM>), g, b, lds, st, o);
         else if (!SMC) hipLaunchKernelGGL((k_sweep_plain<R, CW, DM>), g, b, lds, st, o);
         else hipLaunchKernelGGL((k_sweep<R, CW, false, DM, SMC, false, false>), g, b, lds, st, o);
     }
@@ -2506,24 +2457,30 @@ hipError_t launch_stream_halo(int repr, const HaloArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_acc_fold(const Tile *tiles, int n_tiles, int stream,
-                                                  unsigned long long *acc_tile, unsigned long long *accept)
+__global__ __launch_bounds__(256) void k_acc_fold(const Tile *tiles, int n_tiles, unsigned long long *acc_tile,
+                                                  unsigned long long *accept)
 {
     const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (t >= n_tiles) return;
     const unsigned long long v = acc_tile[t];
     if (v == 0ull) return;
-    const uint32_t sys = stream ? stile_sys(tiles[t]) : tiles[t].sys;
-    atomicAdd(accept + ((int64_t)sys * kAcceptSlots + (t % kAcceptSlots)) * kAcceptStride, v);
+    atomicAdd(accept + ((int64_t)tiles[t].sys * kAcceptSlots + (t % kAcceptSlots)) * kAcceptStride, v);
     acc_tile[t] = 0ull;
 }
 
-hipError_t launch_acc_fold(const Tile *tiles, int n_tiles, bool stream, unsigned long long *acc_tile,
-                           unsigned long long *accept, hipStream_t st)
+hipError_t launch_acc_fold(const Tile *tiles, int n_tiles, unsigned long long *acc_tile, unsigned long long *accept,
+                           hipStream_t st)
 {
     if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_acc_fold, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, tiles, n_tiles,
-                       stream ? 1 : 0, acc_tile, accept);
+    hipLaunchKernelGGL(k_acc_fold, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, st, tiles, n_tiles, acc_tile,
+                       accept);
+    return hipGetLastError();
+}
+
+hipError_t launch_make_tiles(const MakeTilesArgs &a, hipStream_t st)
+{
+    if (a.n_tiles <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_make_tiles, dim3((unsigned)((a.n_tiles + 255) / 256)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -12,19 +12,27 @@ namespace soma {
 constexpr int kStreamLanes = 62;
 
 struct SweepArgs {
+    // (what a wave needs before its position loads comes first, see Head)
+    const Tile *wtiles;            // the tiles of this launch: wave, block or stream tiles
+    const uint64_t *sweep_ctr;     // sweeps done before this graph / launch sequence
     const DevSys *systems;
+    unsigned long long *acc_tile;  // accepted moves per tile (see counts_per_tile), or null
+    int n_wtiles;
+    int waves_per_block;
+    int remap_blocks;              // blocks below this are remapped so that each XCD gets a contiguous
+                                   // range of tiles (a multiple of 8; 0: launch order)
+    uint32_t rel;                  // sweep index relative to *sweep_ctr
+    const uint32_t *chain_id;      // logical chain id (within its system) per chain slot
+    float *P0, *P1, *P2;           // coordinates (F32) or offsets (CELL)
+    int *C0, *C1, *C2;             // cells (CELL only)
     const Tile *tiles;
     int n_tiles;
     const Tile *ptiles;            // block tiles (chains packed over the waves of a block)
     int n_ptiles;
     int packed;                    // 1: one block tile per block; 2: stream tiles, one per wave
                                    // (only with max_blocks == 0)
-    int waves_per_block;
     int max_blocks;                // 0: one tile per wave; else the grid size (waves loop over tiles)
     int xcd_remap;
-    const uint32_t *chain_id;      // logical chain id (within its system) per chain slot
-    float *P0, *P1, *P2;           // coordinates (F32) or offsets (CELL)
-    int *C0, *C1, *C2;             // cells (CELL only)
     uint32_t *base;                // two count buffers of count_words words each
     uint32_t *delta;               // three delta buffers of count_words words each
     int64_t count_words;           // uint32 words per buffer
@@ -37,8 +45,6 @@ struct SweepArgs {
     int smc;                       // some system uses bond-force-biased moves
     int cpl;                       // some system uses walls, zones, the umbrella or caller-set classes
     const float2 *omega;           // frozen fields, per cell (A, B)
-    const uint64_t *sweep_ctr;     // sweeps done before this graph / launch sequence
-    uint32_t rel;                  // sweep index relative to *sweep_ctr
     uint64_t seed;
     unsigned long long *accept;    // [n_sys][kAcceptSlots][kAcceptStride]
     uint32_t *status;
@@ -47,7 +53,6 @@ struct SweepArgs {
     unsigned long long *conv;      // [n_sys][2]: chains converted to class a, to class b
     uint2 *halo;                   // stream tiles: boundary bead pairs, see halo_index
     int64_t halo_cap;              // stream tile entries per halo array
-    unsigned long long *acc_tile;  // accepted moves per tile (see counts_per_tile), or null
 };
 
 // The one-tile-per-wave kernels for uniform moves without coupling (wave
@@ -79,7 +84,6 @@ __host__ __device__ inline int64_t halo_index(int buf, int comp, int64_t tile, i
     return (((int64_t)buf * cap + tile) * 2 + side) * kHaloSlots + comp;
 }
 struct HaloArgs {
-    const DevSys *systems;
     const Tile *ptiles;
     int n_ptiles;
     float *P0, *P1, *P2;           // read only
@@ -179,9 +183,18 @@ struct ObsArgs {
 
 hipError_t launch_sweep(int repr, int cw, const SweepArgs &a, hipStream_t st);
 hipError_t launch_stream_halo(int repr, const HaloArgs &a, hipStream_t st);
-// Add acc_tile[t] to the acceptance counters of tile t's system and clear it
-// (stream: the tiles are stream tiles, whose system is the low 24 bits).
-hipError_t launch_acc_fold(const Tile *tiles, int n_tiles, bool stream, unsigned long long *acc_tile,
+// Write the tile table of a context: kind 0 wave tiles, 1 block tiles of
+// `lanes` lanes, 2 stream tiles; first[k] is the first tile of system k
+// (first[n_sys] = n_tiles).
+struct MakeTilesArgs {
+    const DevSys *systems;
+    const int32_t *first;
+    int n_sys, n_tiles, kind, lanes;
+    Tile *tiles;
+};
+hipError_t launch_make_tiles(const MakeTilesArgs &a, hipStream_t st);
+// Add acc_tile[t] to the acceptance counters of tile t's system and clear it.
+hipError_t launch_acc_fold(const Tile *tiles, int n_tiles, unsigned long long *acc_tile,
                            unsigned long long *accept, hipStream_t st);
 hipError_t launch_density(int repr, int cw, const DensityArgs &a, hipStream_t st);
 hipError_t launch_fields(int cw, const FieldArgs &a, hipStream_t st);

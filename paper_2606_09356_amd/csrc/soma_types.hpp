@@ -54,8 +54,8 @@ struct alignas(16) DevSys {
     float k_half;          // k/2 = 3(N-1)/(2 Re^2)
     float delta;           // move half-width
     float inv_P;           // 1 / P
-    // omega_A = cAA nA + cAB nB + c0, omega_B = cBA nA + cBB nB + c0
-    float cAA, cAB, cBA, cBB, c0;
+    // omega_A = c_same nA + c_other nB + c0, omega_B = c_other nA + c_same nB + c0
+    float c_same, c_other, c0;
     int64_t n_cells;
     // bond-force-biased moves (smc != 0): displacement A F + sqrt(2A) xi in
     // FP64, rejected at 0.99 cell edges; the acceptance ratio in FP32
@@ -82,9 +82,24 @@ struct alignas(16) DevSys {
     alignas(16) uint32_t pat_b[kPatternWords];
 };
 
-struct Tile {
+// One tile of the sweep (wave, block or stream tile): everything a wave needs
+// to address its beads, so that the position loads go out one scalar load
+// after the kernel's arguments (they do not wait for the system table).
+// Consecutive lanes of a tile hold consecutive bead pairs.
+struct alignas(32) Tile {
     uint32_t sys;          // index into the system table (not the Philox system id)
-    uint32_t chain0;       // first chain of the tile within its system
+    int32_t chain0;        // chain (within its system) of lane 0; stream tiles: one before that of lane 1
+    int64_t slot;          // bead slot of lane 0's pair (lane l: 2 l further)
+    int64_t chain;         // context-wide chain slot of chain0
+    uint32_t lanes;        // see tile_word
+    float inv_P;           // 1 / P
 };
+// lanes word: bits 0..10 number of lanes with a bead pair (stream tiles: end
+// of the valid lanes), 11..17 P, 18 lane 0 is valid, 24..31 pair index of
+// lane 0 within chain0 (stream tiles: plus P, counted from chain0)
+__host__ __device__ inline uint32_t tile_word(uint32_t n, uint32_t P, bool first, uint32_t q)
+{
+    return n | P << 11 | (first ? 1u << 18 : 0u) | q << 24;
+}
 
 }  // namespace soma
