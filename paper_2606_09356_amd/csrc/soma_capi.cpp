@@ -60,7 +60,7 @@ struct Layout {
     int n_tiles = 0;
     int n_ptiles_cap = 0;   // entries of the block/stream tile table
     int n_chunks = 0;      // fold chunks of density mode 2
-    int64_t max_obs_blocks = 0, max_cells = 0;
+    int64_t max_cells = 0;
 };
 
 struct HostSys {
@@ -164,7 +164,7 @@ struct soma_ctx {
     uint2 *halo() const { return reinterpret_cast<uint2 *>(ws + L.halo); }
     unsigned long long *acc_tile() const { return reinterpret_cast<unsigned long long *>(ws + L.acc_tile); }
     double *partials() const { return reinterpret_cast<double *>(ws + L.partials); }
-    double *obs_out() const { return reinterpret_cast<double *>(ws + L.obs_out); }
+    soma::ObsResult *obs_out() const { return reinterpret_cast<soma::ObsResult *>(ws + L.obs_out); }
     void *staging() const { return ws + L.staging; }
     uint8_t *chain_class() const { return reinterpret_cast<uint8_t *>(ws + L.chain_class); }
     uint8_t *chain_class2() const { return reinterpret_cast<uint8_t *>(ws + L.chain_class2); }
@@ -274,7 +274,7 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     Layout L{};
     int64_t slots = 0, cells = 0, chains = 0, beads = 0, stiles = 0;
     int tiles = 0;
-    int64_t max_blocks = 1, max_cells = 1;
+    int64_t max_cells = 1;
     for (int32_t k = 0; k < n_sys; ++k) {
         const soma_system_desc &d = sys[k];
         const int P = (d.N + 1) / 2, G = soma::kWave / P;
@@ -348,7 +348,6 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
         beads += (int64_t)d.n_chains * d.N;
         tiles += nt;
         stiles += ((int64_t)d.n_chains * P + soma::kStreamLanes - 1) / soma::kStreamLanes;
-        max_blocks = std::max<int64_t>(max_blocks, (d.n_chains + 255) / 256 + (M + 255) / 256);
         max_cells = std::max<int64_t>(max_cells, M);
     }
     const bool cell = opt->pos_repr == SOMA_POS_CELL_F32;
@@ -358,7 +357,6 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     L.total_beads = beads;
     L.n_tiles = tiles;
     L.count_words = cells * (opt->count_width == SOMA_COUNT_U16 ? 1 : 2);
-    L.max_obs_blocks = max_blocks;
     L.max_cells = max_cells;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
@@ -399,8 +397,8 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     L.halo = take(sizeof(uint2) * 2 * soma::kHaloSlots * 2 * (size_t)L.n_ptiles_cap);
     // accepted moves per wave or stream tile (counts_per_tile)
     L.acc_tile = take(sizeof(unsigned long long) * (size_t)std::max<int64_t>(tiles, L.n_ptiles_cap));
-    L.partials = take(sizeof(double) * 12 * max_blocks);
-    L.obs_out = take(sizeof(double) * 8);
+    L.partials = take(sizeof(double) * soma::kObsPartials);
+    L.obs_out = take(sizeof(soma::ObsResult));
     L.staging = take(sizeof(float) * 2 * max_cells);
     L.chain_class = take(sizeof(uint8_t) * chains);
     L.chain_class2 = take(sizeof(uint8_t) * chains);     // autotune save
@@ -429,17 +427,23 @@ int check_sys(soma_ctx *c, int32_t sys)
     return SOMA_OK;
 }
 
-// Synchronise and turn latched device status bits into an error code.
-int sync_status(soma_ctx *c)
+// Turn device status bits into an error code and latch it.
+int status_error(soma_ctx *c, uint32_t st)
 {
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    uint32_t st = 0;
-    HIPCHK(c, hipMemcpy(&st, c->status(), sizeof st, hipMemcpyDeviceToHost));
     if (st & soma::ST_COUNT_OVERFLOW) { c->latched = SOMA_EOVERFLOW; return fail(c, SOMA_EOVERFLOW, "density count exceeded its width"); }
     if (st & soma::ST_CELL_OVERFLOW) { c->latched = SOMA_EOVERFLOW; return fail(c, SOMA_EOVERFLOW, "bead cell index left the int32 range (or a coordinate is not finite)"); }
     if (st & soma::ST_INTERNAL) { c->latched = SOMA_EDEVICE; return fail(c, SOMA_EDEVICE, "internal consistency check failed in the chain reorder"); }
     if (st & soma::ST_PLACEMENT) { c->latched = SOMA_EINVAL; return fail(c, SOMA_EINVAL, "chains do not fit between the walls (64 attempts each)"); }
     return SOMA_OK;
+}
+
+// Synchronise and report latched device status bits.
+int sync_status(soma_ctx *c)
+{
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    uint32_t st = 0;
+    HIPCHK(c, hipMemcpy(&st, c->status(), sizeof st, hipMemcpyDeviceToHost));
+    return status_error(c, st);
 }
 
 // Launch shape of the sweep kernel: waves per workgroup, resident grid
@@ -1059,9 +1063,8 @@ int run_sweeps(soma_ctx *c, int32_t n, hipEvent_t *ev)
 }
 
 // The observables of one system, with the block partial sums in `partials`
-// (12 doubles per block: ceil(n_chains/256) + ceil(n_cells/256) blocks) and
-// the six sums in `result`; allocates nothing.
-int observables_into(soma_ctx *c, int32_t sys, soma_obs *out, double *partials, double *result)
+// (kObsPartials doubles) and the sums in `result`; allocates nothing.
+int observables_into(soma_ctx *c, int32_t sys, soma_obs *out, double *partials, soma::ObsResult *result)
 {
     int rc = fold_acc(c);
     if (rc != SOMA_OK) return rc;
@@ -1069,11 +1072,10 @@ int observables_into(soma_ctx *c, int32_t sys, soma_obs *out, double *partials, 
     if (rc != SOMA_OK) return rc;
     const HostSys &h = c->sys[sys];
     soma::ObsArgs a{};
-    a.repr = c->repr;
-    a.n_chains = h.d.n_chains;
+    a.tiles = c->d_tiles();
+    a.tile_begin = h.tile_begin;
+    a.tile_end = h.tile_end;
     a.N = h.d.N;
-    a.stride = 2 * h.dev.P;
-    a.slot_off = h.dev.slot_off;
     for (int d = 0; d < 3; ++d) {
         a.edge[d] = h.dev.edge[d];
         (&a.P0)[d] = c->P(d);
@@ -1091,31 +1093,27 @@ int observables_into(soma_ctx *c, int32_t sys, soma_obs *out, double *partials, 
     a.umb_lambda = h.dev.umb ? h.umb_lambda : 0.0;
     a.tgt = c->tgt();
     a.partials = partials;
-    a.block_base = 0;
-    HIPCHK(c, soma::launch_observables(c->cw, a, result, c->stream));
-    double q[6];
-    unsigned long long conv[2] = {0, 0};
-    unsigned long long slots[soma::kAcceptSlots * soma::kAcceptStride];
-    HIPCHK(c, hipMemcpyAsync(q, result, sizeof q, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(conv, c->conv() + 2 * (size_t)sys, sizeof conv, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(slots, c->accept() + (size_t)sys * soma::kAcceptSlots * soma::kAcceptStride,
-                             sizeof slots, hipMemcpyDeviceToHost, c->stream));
-    if ((rc = sync_status(c)) != SOMA_OK) return rc;
-    unsigned long long acc = 0;
-    for (int k = 0; k < soma::kAcceptSlots; ++k) acc += slots[(size_t)k * soma::kAcceptStride];
+    a.accept = c->accept() + (size_t)sys * soma::kAcceptSlots * soma::kAcceptStride;
+    a.conv = c->conv() + 2 * (size_t)sys;
+    a.status = c->status();
+    HIPCHK(c, soma::launch_observables(c->repr, c->cw, a, result, c->stream));
+    soma::ObsResult r;
+    HIPCHK(c, hipMemcpyAsync(&r, result, sizeof r, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if ((rc = status_error(c, r.status)) != SOMA_OK) return rc;
     const double n = (double)h.d.n_chains;
-    out->Re2 = q[0] / n;
-    out->Re2_err = std::sqrt(std::max(q[1] / n - out->Re2 * out->Re2, 0.0) / n);
-    out->Rg2 = q[2] / n;
-    out->Rg2_err = std::sqrt(std::max(q[3] / n - out->Rg2 * out->Rg2, 0.0) / n);
-    out->Ebond_per_chain = q[4] / n;
-    out->Enb_per_chain = (B / (double)h.dev.n_cells) / h.d.N * q[5] / n;
+    out->Re2 = r.q[0] / n;
+    out->Re2_err = std::sqrt(std::max(r.q[1] / n - out->Re2 * out->Re2, 0.0) / n);
+    out->Rg2 = r.q[2] / n;
+    out->Rg2_err = std::sqrt(std::max(r.q[3] / n - out->Rg2 * out->Rg2, 0.0) / n);
+    out->Ebond_per_chain = r.q[4] / n;
+    out->Enb_per_chain = (B / (double)h.dev.n_cells) / h.d.N * r.q[5] / n;
     out->sweep = c->sweep;
     out->n_moves = (uint64_t)(c->swept * (uint64_t)B);
-    out->n_accepted = acc;
-    out->accept_ratio = out->n_moves ? (double)acc / (double)out->n_moves : 0.0;
-    out->converted_to_a = conv[0];
-    out->converted_to_b = conv[1];
+    out->n_accepted = r.accepted;
+    out->accept_ratio = out->n_moves ? (double)r.accepted / (double)out->n_moves : 0.0;
+    out->converted_to_a = r.conv[0];
+    out->converted_to_b = r.conv[1];
     return SOMA_OK;
 }
 
@@ -1343,10 +1341,12 @@ int soma_observables_noalloc(soma_ctx *c, int32_t sys, soma_obs *out)
         return fail(c, SOMA_EINVAL, "the context's device must be the current device");
     const HostSys &h = c->sys[sys];
     const size_t blocks = (size_t)(h.d.n_chains + 255) / 256 + (size_t)(h.dev.n_cells + 255) / 256;
+    static_assert(soma::kObsPartials + sizeof(soma::ObsResult) / 8 <= kScratchDoubles, "scratch size");
     if (12 * blocks > kScratchDoubles - 8)
         return fail(c, SOMA_EINVAL, "system too large for the static scratch: ceil(n_chains/256) + "
                                     "ceil(n_cells/256) must be at most 10922 blocks");
-    return observables_into(c, sys, out, c->scratch_dev, c->scratch_dev + (kScratchDoubles - 8));
+    return observables_into(c, sys, out, c->scratch_dev,
+                            reinterpret_cast<soma::ObsResult *>(c->scratch_dev + soma::kObsPartials));
 }
 
 int soma_get_positions(soma_ctx *c, int32_t sys, double *xyz)

@@ -163,13 +163,13 @@ struct PlaceArgs {
 };
 
 struct ObsArgs {
-    int repr;
-    int n_chains, N, stride;
-    int64_t slot_off;
+    const Tile *tiles;             // wave tiles
+    int tile_begin, tile_end;      // of the system
+    int N;
     float edge[3];
     double k_half;
-    const float *P0, *P1, *P2;
-    const int *C0, *C1, *C2;
+    float *P0, *P1, *P2;
+    int *C0, *C1, *C2;
     const uint32_t *counts;        // current counts
     int64_t cell_off, n_cells;
     double phi_per_count;          // M / B
@@ -177,9 +177,20 @@ struct ObsArgs {
     int ham_form;
     double umb_lambda;             // umbrella strength (0: off)
     const float2 *tgt;             // umbrella targets per cell of the context
-    double *partials;
-    int block_base;
+    double *partials;              // kObsPartials doubles
+    int chain_blocks, cell_blocks; // set by the launcher
+    const unsigned long long *accept;   // the system's acceptance slots
+    const unsigned long long *conv;     // the system's two conversion counters
+    const uint32_t *status;
 };
+// What the observable kernels leave for the host.
+struct ObsResult {
+    double q[6];                   // sums over chains of Re2, Re2^2, Rg2, Rg2^2, Ebond; over cells of the energy density
+    unsigned long long conv[2], accepted;
+    uint32_t status, pad;
+};
+constexpr int kObsBlocks = 1280;   // most blocks of either part (five per compute unit)
+constexpr int64_t kObsPartials = (int64_t)12 * kObsBlocks;
 
 hipError_t launch_sweep(int repr, int cw, const SweepArgs &a, hipStream_t st);
 hipError_t launch_stream_halo(int repr, const HaloArgs &a, hipStream_t st);
@@ -247,7 +258,7 @@ hipError_t launch_init(const InitArgs &a, hipStream_t st);
 hipError_t launch_iota_chains(const ReorderArgs &a, hipStream_t st);
 hipError_t launch_reorder(int repr, const ReorderArgs &a, hipStream_t st);
 int64_t reorder_bsum_words(int64_t total_cells);
-hipError_t launch_observables(int cw, const ObsArgs &a, double *out, hipStream_t st);
+hipError_t launch_observables(int repr, int cw, const ObsArgs &a, ObsResult *out, hipStream_t st);
 hipError_t launch_place(const PlaceArgs &a, unsigned long long *scan_bsum, hipStream_t st);
 int64_t place_bsum_words(int64_t n_cells);
 
