@@ -974,28 +974,27 @@ int fetch_classes(soma_ctx *c, const HostSys &h, std::vector<uint8_t> &cls)
     return SOMA_OK;
 }
 
-// Stored slots of one system in logical chain order (chain L at L * stride).
-int download_slots(soma_ctx *c, const HostSys &h, std::vector<float> (&P)[3], std::vector<int> (&Cv)[3])
+// Arguments of the state kernels of one system; the compact buffers lie in
+// the reorder's scratch (12 or 24 bytes per slot in one piece, free between
+// reorders).
+soma::StateArgs state_args(const soma_ctx *c, const HostSys &h)
 {
-    const size_t stride = 2 * (size_t)h.dev.P, n = (size_t)h.d.n_chains * stride;
-    std::vector<uint32_t> cid;
-    int rc = fetch_chain_ids(c, h, cid);
-    if (rc != SOMA_OK) return rc;
-    std::vector<float> fp(n);
-    std::vector<int> ip(n);
-    for (int a = 0; a < 3; ++a) {
-        HIPCHK(c, hipMemcpyAsync(fp.data(), c->P(a) + h.dev.slot_off, n * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-        if (c->repr == soma::REPR_CELL)
-            HIPCHK(c, hipMemcpyAsync(ip.data(), c->C(a) + h.dev.slot_off, n * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        P[a].resize(n);
-        if (c->repr == soma::REPR_CELL) Cv[a].resize(n);
-        for (size_t j = 0; j < cid.size(); ++j) {
-            std::memcpy(&P[a][cid[j] * stride], &fp[j * stride], stride * sizeof(float));
-            if (c->repr == soma::REPR_CELL) std::memcpy(&Cv[a][cid[j] * stride], &ip[j * stride], stride * sizeof(int));
-        }
+    soma::StateArgs a{};
+    a.systems = c->d_sys();
+    a.tiles = c->d_tiles();
+    a.chain_id = c->chain_id();
+    a.tile_begin = h.tile_begin;
+    a.tile_end = h.tile_end;
+    for (int d = 0; d < 3; ++d) {
+        (&a.P0)[d] = c->P(d);
+        (&a.C0)[d] = c->C(d);
     }
-    return SOMA_OK;
+    a.f = c->Q(0);
+    a.c = c->D(0);
+    a.xyz = reinterpret_cast<double *>(c->Q(0));
+    a.flags = c->status() + 4;
+    a.status = c->status();
+    return a;
 }
 
 // Upload slots given in logical chain order to the current physical order.
@@ -1356,19 +1355,13 @@ int soma_get_positions(soma_ctx *c, int32_t sys, double *xyz)
     if ((rc = check_sys(c, sys)) != SOMA_OK) return rc;
     if (!xyz) return fail(c, SOMA_EINVAL, "xyz is null");
     const HostSys &h = c->sys[sys];
-    std::vector<float> P[3];
-    std::vector<int> Cv[3];
-    if ((rc = download_slots(c, h, P, Cv)) != SOMA_OK) return rc;
-    const int N = h.d.N, stride = 2 * h.dev.P;
-    const int64_t B = (int64_t)h.d.n_chains * N;
-    for (int a = 0; a < 3; ++a)
-        for (int64_t ch = 0; ch < h.d.n_chains; ++ch)
-            for (int i = 0; i < N; ++i) {
-                const size_t s = (size_t)(ch * stride + i);
-                xyz[a * B + ch * N + i] = c->repr == soma::REPR_F32
-                                              ? (double)P[a][s]
-                                              : (double)Cv[a][s] * (double)h.dev.edge[a] + (double)P[a][s];
-            }
+    const int64_t B = (int64_t)h.d.n_chains * h.d.N;
+    soma::StateArgs a = state_args(c, h);
+    // one axis at a time: the scratch holds 12 bytes per slot with FP32 positions
+    for (a.axis = 0; a.axis < 3; ++a.axis) {
+        HIPCHK(c, soma::launch_export_positions(c->repr, a, c->stream));
+        HIPCHK(c, hipMemcpyAsync(xyz + a.axis * B, a.xyz, sizeof(double) * (size_t)B, hipMemcpyDeviceToHost, c->stream));
+    }
     return sync_status(c);
 }
 
@@ -1410,18 +1403,12 @@ int soma_get_state(soma_ctx *c, int32_t sys, float *f32, int32_t *cell)
     if ((rc = check_sys(c, sys)) != SOMA_OK) return rc;
     if (!f32 || (c->repr == soma::REPR_CELL && !cell)) return fail(c, SOMA_EINVAL, "null state buffer");
     const HostSys &h = c->sys[sys];
-    std::vector<float> P[3];
-    std::vector<int> Cv[3];
-    if ((rc = download_slots(c, h, P, Cv)) != SOMA_OK) return rc;
-    const int N = h.d.N, stride = 2 * h.dev.P;
-    const int64_t B = (int64_t)h.d.n_chains * N;
-    for (int a = 0; a < 3; ++a)
-        for (int64_t ch = 0; ch < h.d.n_chains; ++ch)
-            for (int i = 0; i < N; ++i) {
-                const size_t s = (size_t)(ch * stride + i);
-                f32[a * B + ch * N + i] = P[a][s];
-                if (c->repr == soma::REPR_CELL) cell[a * B + ch * N + i] = Cv[a][s];
-            }
+    const size_t words = 3 * (size_t)h.d.n_chains * h.d.N;
+    const soma::StateArgs a = state_args(c, h);
+    HIPCHK(c, soma::launch_export_state(c->repr, a, c->stream));
+    HIPCHK(c, hipMemcpyAsync(f32, a.f, sizeof(float) * words, hipMemcpyDeviceToHost, c->stream));
+    if (c->repr == soma::REPR_CELL)
+        HIPCHK(c, hipMemcpyAsync(cell, a.c, sizeof(int32_t) * words, hipMemcpyDeviceToHost, c->stream));
     return sync_status(c);
 }
 
@@ -1432,38 +1419,24 @@ int soma_set_state(soma_ctx *c, int32_t sys, const float *f32, const int32_t *ce
     if ((rc = check_sys(c, sys)) != SOMA_OK) return rc;
     if (!f32 || (c->repr == soma::REPR_CELL && !cell)) return fail(c, SOMA_EINVAL, "null state buffer");
     const HostSys &h = c->sys[sys];
-    const int N = h.d.N, stride = 2 * h.dev.P;
-    const int64_t B = (int64_t)h.d.n_chains * N;
-    std::vector<float> P[3];
-    std::vector<int> Cv[3];
-    for (int a = 0; a < 3; ++a) {
-        P[a].assign((size_t)h.d.n_chains * stride, 0.0f);
-        if (c->repr == soma::REPR_CELL) Cv[a].assign((size_t)h.d.n_chains * stride, 0);
-        for (int64_t ch = 0; ch < h.d.n_chains; ++ch)
-            for (int i = 0; i < N; ++i) {
-                const size_t s = (size_t)(ch * stride + i);
-                const float v = f32[a * B + ch * N + i];
-                if (!std::isfinite(v)) return fail(c, SOMA_EINVAL, "state values must be finite");
-                if (c->repr == soma::REPR_CELL) {
-                    const int cv = cell[a * B + ch * N + i];
-                    if (!(v >= -h.dev.edge[a] && v < 2.0f * h.dev.edge[a]))
-                        return fail(c, SOMA_EINVAL, "offsets must lie in [-edge, 2 edge)");
-                    if (cv <= -(1 << 22) || cv >= (1 << 22)) return fail(c, SOMA_EINVAL, "cell index out of range (|cell| < 2^22)");
-                    Cv[a][s] = cv;
-                }
-                P[a][s] = v;
-            }
-    }
-    if (h.dev.walls) {
-        std::vector<int> zc((size_t)B);
-        for (int64_t ch = 0, j = 0; ch < h.d.n_chains; ++ch)
-            for (int i = 0; i < N; ++i, ++j) {
-                const size_t sl = (size_t)(ch * stride + i);
-                zc[(size_t)j] = c->repr == soma::REPR_CELL ? Cv[2][sl] : z_floor(P[2][sl], h.dev.edge[2]);
-            }
-        if (!inside_walls(h, zc)) return fail(c, SOMA_EINVAL, "state outside the walls");
-    }
-    if ((rc = upload_slots(c, h, P, Cv)) != SOMA_OK) return rc;
+    const size_t words = 3 * (size_t)h.d.n_chains * h.d.N;
+    const soma::StateArgs a = state_args(c, h);
+    HIPCHK(c, hipMemcpyAsync(a.f, f32, sizeof(float) * words, hipMemcpyHostToDevice, c->stream));
+    if (c->repr == soma::REPR_CELL)
+        HIPCHK(c, hipMemcpyAsync(a.c, cell, sizeof(int32_t) * words, hipMemcpyHostToDevice, c->stream));
+    // nothing of the system changes before its new state has been checked
+    HIPCHK(c, soma::launch_fill_u32(a.flags, 1, 0u, c->stream));
+    HIPCHK(c, soma::launch_check_state(c->repr, a, c->stream));
+    uint32_t st[5] = {};     // the status word and the check's flags
+    HIPCHK(c, hipMemcpyAsync(st, c->status(), sizeof st, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (st[4] & soma::ST_BAD_VALUE) return fail(c, SOMA_EINVAL, "state values must be finite");
+    if (st[4] & soma::ST_BAD_OFFSET) return fail(c, SOMA_EINVAL, "offsets must lie in [-edge, 2 edge)");
+    if (st[4] & soma::ST_BAD_CELL) return fail(c, SOMA_EINVAL, "cell index out of range (|cell| < 2^22)");
+    if (st[4] & soma::ST_BAD_WALL) return fail(c, SOMA_EINVAL, "state outside the walls");
+    if ((rc = status_error(c, st[0])) != SOMA_OK) return rc;
+    c->halo_sweep = ~uint64_t(0);
+    HIPCHK(c, soma::launch_import_state(c->repr, a, c->stream));
     if ((rc = rebuild_density(c, sys)) != SOMA_OK) return rc;
     return sync_status(c);
 }

@@ -1708,6 +1708,127 @@ __global__ __launch_bounds__(256) void k_density(DensityArgs a)
     if (ovf) atomicOr(a.status, ST_COUNT_OVERFLOW);
 }
 
+// ---------------------------------------------------------------------------
+// State transfer (checkpoints): the chains' order and the padding are undone
+// and redone here, so the host copies one compact block straight from or to
+// the caller's memory.  (The permutation on the host took 40 of the 46 ms of
+// a 4.2M-bead cell + offset state; these kernels take tens of microseconds.)
+// ---------------------------------------------------------------------------
+// The compact index of a lane's pair, or -1 (no pair, or a corrupt chain id).
+__device__ __forceinline__ int64_t compact_index(const StateArgs &a, const Tile &T, SysPtr S, const TileLane &L)
+{
+    if (!L.valid) return -1;
+    const uint32_t clog = a.chain_id[T.chain + L.g];
+    if (clog >= (uint32_t)S->n_chains) {
+        atomicOr(a.status, ST_INTERNAL);
+        return -1;
+    }
+    return (int64_t)clog * S->N + 2 * L.p;
+}
+
+template <class V>
+__device__ __forceinline__ void put_pair(V *dst, int64_t i, bool two, V a, V b)
+{
+    dst[i] = a;
+    if (two) dst[i + 1] = b;
+}
+__device__ __forceinline__ void put_state(const StateArgs &a, int64_t B, int64_t i, bool two, const BeadF32 &u, const BeadF32 &w)
+{
+    put_pair(a.f, i, two, u.x, w.x);
+    put_pair(a.f + B, i, two, u.y, w.y);
+    put_pair(a.f + 2 * B, i, two, u.z, w.z);
+}
+__device__ __forceinline__ void put_state(const StateArgs &a, int64_t B, int64_t i, bool two, const BeadCell &u,
+                                          const BeadCell &w)
+{
+    put_pair(a.f, i, two, u.ox, w.ox);
+    put_pair(a.f + B, i, two, u.oy, w.oy);
+    put_pair(a.f + 2 * B, i, two, u.oz, w.oz);
+    put_pair(a.c, i, two, u.cx, w.cx);
+    put_pair(a.c + B, i, two, u.cy, w.cy);
+    put_pair(a.c + 2 * B, i, two, u.cz, w.cz);
+}
+// (the padding slot of an odd chain holds a zero bead)
+__device__ __forceinline__ void get_state(const StateArgs &a, int64_t B, int64_t i, bool two, BeadF32 &u, BeadF32 &w)
+{
+    u = BeadF32{a.f[i], a.f[B + i], a.f[2 * B + i]};
+    w = BeadF32{0.0f, 0.0f, 0.0f};
+    if (two) w = BeadF32{a.f[i + 1], a.f[B + i + 1], a.f[2 * B + i + 1]};
+}
+__device__ __forceinline__ void get_state(const StateArgs &a, int64_t B, int64_t i, bool two, BeadCell &u, BeadCell &w)
+{
+    u = BeadCell{a.c[i], a.c[B + i], a.c[2 * B + i], a.f[i], a.f[B + i], a.f[2 * B + i]};
+    w = BeadCell{0, 0, 0, 0.0f, 0.0f, 0.0f};
+    if (two) w = BeadCell{a.c[i + 1], a.c[B + i + 1], a.c[2 * B + i + 1], a.f[i + 1], a.f[B + i + 1], a.f[2 * B + i + 1]};
+}
+
+enum { STATE_OUT, STATE_POS, STATE_CHECK, STATE_IN };
+
+__device__ __forceinline__ double axis64(const BeadF32 &b, int d, SysPtr) { return (double)(d == 0 ? +b.x : d == 1 ? +b.y : +b.z); }
+__device__ __forceinline__ double axis64(const BeadCell &b, int d, SysPtr S)
+{
+    return (double)(d == 0 ? +b.cx : d == 1 ? +b.cy : +b.cz) * (double)S->edge[d] + (double)(d == 0 ? +b.ox : d == 1 ? +b.oy : +b.oz);
+}
+
+// What is wrong with a bead set from the host.
+__device__ __forceinline__ bool finite3(float x, float y, float z)
+{
+    const float m = __uint_as_float(0x7F7FFFFFu);   // FLT_MAX; a NaN fails the comparison
+    return fabsf(x) <= m && fabsf(y) <= m && fabsf(z) <= m;
+}
+__device__ __forceinline__ uint32_t state_flaws(const BeadF32 &b, SysPtr S)
+{
+    if (!finite3(b.x, b.y, b.z)) return ST_BAD_VALUE;
+    if (!S->walls) return 0u;
+    const BeadF32 one[1] = {b};
+    int k[1][3];
+    ngp_index(one, make_view(S), k);
+    return k[0][2] < S->wall_lo || k[0][2] >= S->wall_hi ? (uint32_t)ST_BAD_WALL : 0u;
+}
+__device__ __forceinline__ uint32_t state_flaws(const BeadCell &b, SysPtr S)
+{
+    if (!finite3(b.ox, b.oy, b.oz)) return ST_BAD_VALUE;
+    uint32_t f = 0u;
+    if (!(b.ox >= -S->edge[0] && b.ox < 2.0f * S->edge[0] && b.oy >= -S->edge[1] && b.oy < 2.0f * S->edge[1] &&
+          b.oz >= -S->edge[2] && b.oz < 2.0f * S->edge[2]))
+        f |= ST_BAD_OFFSET;
+    const int lim = kStateCellLimit;
+    if (b.cx <= -lim || b.cx >= lim || b.cy <= -lim || b.cy >= lim || b.cz <= -lim || b.cz >= lim) f |= ST_BAD_CELL;
+    if (S->walls && (b.cz < S->wall_lo || b.cz >= S->wall_hi)) f |= ST_BAD_WALL;
+    return f;
+}
+
+template <int R, int OP>
+__global__ __launch_bounds__(256) void k_state(StateArgs a)
+{
+    using Bead = typename std::conditional<R == REPR_F32, BeadF32, BeadCell>::type;
+    const int wave = __builtin_amdgcn_readfirstlane(
+        a.tile_begin + (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    if (wave >= a.tile_end) return;
+    const Tile T = tile_at(a.tiles, wave);
+    const SysPtr S = sys_at(a.systems, T.sys);
+    const TileLane L = lane_of<TIL_WAVE>(T);
+    const int64_t i = compact_index(a, T, S, L);
+    if (i < 0) return;
+    const bool two = 2 * L.p + 1 < S->N;
+    const int64_t B = (int64_t)S->n_chains * S->N;
+    const uint32_t off = (uint32_t)tile_lane<TIL_WAVE>() * 8u;
+    Bead u, w;
+    if constexpr (OP == STATE_OUT || OP == STATE_POS) {
+        load_pair(pos_arrays(a), T.slot, off, u, w);
+        if constexpr (OP == STATE_OUT) put_state(a, B, i, two, u, w);
+        else put_pair(a.xyz, i, two, axis64(u, a.axis, S), axis64(w, a.axis, S));
+    } else {
+        get_state(a, B, i, two, u, w);
+        if constexpr (OP == STATE_CHECK) {
+            const uint32_t f = state_flaws(u, S) | (two ? state_flaws(w, S) : 0u);
+            if (f) atomicOr(a.flags, f);
+        } else {
+            store_pair(pos_arrays(a), T.slot, off, u, w);
+        }
+    }
+}
+
 // Fields of one system as float [2][M] (A then B), from its counts or its
 // frozen array.
 template <int CW>
@@ -2501,6 +2622,21 @@ hipError_t launch_density(int repr, int cw, const DensityArgs &a, hipStream_t st
     }
     return hipGetLastError();
 }
+
+template <int OP>
+static hipError_t launch_state(int repr, const StateArgs &a, hipStream_t st)
+{
+    const int n = a.tile_end - a.tile_begin;
+    if (n <= 0) return hipSuccess;
+    const dim3 g((n + 3) / 4), b(256);
+    if (repr == REPR_F32) hipLaunchKernelGGL((k_state<REPR_F32, OP>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_state<REPR_CELL, OP>), g, b, 0, st, a);
+    return hipGetLastError();
+}
+hipError_t launch_export_state(int repr, const StateArgs &a, hipStream_t st) { return launch_state<STATE_OUT>(repr, a, st); }
+hipError_t launch_export_positions(int repr, const StateArgs &a, hipStream_t st) { return launch_state<STATE_POS>(repr, a, st); }
+hipError_t launch_check_state(int repr, const StateArgs &a, hipStream_t st) { return launch_state<STATE_CHECK>(repr, a, st); }
+hipError_t launch_import_state(int repr, const StateArgs &a, hipStream_t st) { return launch_state<STATE_IN>(repr, a, st); }
 
 hipError_t launch_fields(int cw, const FieldArgs &a, hipStream_t st)
 {

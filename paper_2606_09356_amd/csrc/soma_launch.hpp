@@ -192,6 +192,27 @@ struct ObsResult {
 constexpr int kObsBlocks = 1280;   // most blocks of either part (five per compute unit)
 constexpr int64_t kObsPartials = (int64_t)12 * kObsBlocks;
 
+// The stored state of one system between its slots (physical chain order,
+// padded stride) and a compact buffer of the workspace in logical chain
+// order, [3][n_chains N] words.
+struct StateArgs {
+    const DevSys *systems;
+    const Tile *tiles;             // wave tiles
+    const uint32_t *chain_id;
+    int tile_begin, tile_end;
+    float *P0, *P1, *P2;
+    int *C0, *C1, *C2;
+    float *f;                      // coordinates or offsets
+    int *c;                        // cells (CELL)
+    double *xyz;                   // one axis of the FP64 positions
+    int axis;
+    uint32_t *flags;               // import check: ST_BAD_* bits
+    uint32_t *status;
+};
+hipError_t launch_export_state(int repr, const StateArgs &a, hipStream_t st);
+hipError_t launch_export_positions(int repr, const StateArgs &a, hipStream_t st);
+hipError_t launch_check_state(int repr, const StateArgs &a, hipStream_t st);
+hipError_t launch_import_state(int repr, const StateArgs &a, hipStream_t st);
 hipError_t launch_sweep(int repr, int cw, const SweepArgs &a, hipStream_t st);
 hipError_t launch_stream_halo(int repr, const HaloArgs &a, hipStream_t st);
 // Write the tile table of a context: kind 0 wave tiles, 1 block tiles of

@@ -29,6 +29,10 @@ enum StatusBits : uint32_t {
     ST_PLACEMENT = 16u,     // a chain did not fit between the walls (initial walks, placement)
 };
 
+// What the check of a state set from the host finds.
+enum StateBits : uint32_t { ST_BAD_VALUE = 1u, ST_BAD_OFFSET = 2u, ST_BAD_CELL = 4u, ST_BAD_WALL = 8u };
+constexpr int kStateCellLimit = 1 << 22;   // |cell| of a state set from the host stays below this
+
 // Attempts of the initial walks and of the placement to draw a chain that
 // fits between walls.
 constexpr int kMaxAttempts = 64;
