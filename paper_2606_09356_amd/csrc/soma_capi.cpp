@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -49,6 +50,62 @@ double *scratch_for_device(int dev)
         g_scratch_ptr[dev] = static_cast<double *>(p);
     }
     return g_scratch_ptr[dev];
+}
+
+// Pinned host memory of a context: what its kernels report to the host
+// without a copy command (a 4-byte copy took 11 of the 12 us of a call that
+// only waits).  Blocks come from slabs shared by the process's contexts; a
+// slab without blocks in use is freed, but for the last one.
+struct alignas(256) HostBlock {
+    soma::ObsResult obs;
+    uint32_t status;
+};
+constexpr int kSlabBlocks = 64;
+struct Slab {
+    HostBlock *mem;
+    uint64_t used;             // bit per block
+};
+std::mutex g_slab_mu;
+std::vector<Slab> g_slabs;
+
+// nullptr if no pinned memory is to be had (the context then copies).
+HostBlock *host_block_take()
+{
+    std::lock_guard<std::mutex> lk(g_slab_mu);
+    for (Slab &s : g_slabs)
+        if (~s.used) {
+            const int k = __builtin_ctzll(~s.used);
+            s.used |= uint64_t(1) << k;
+            return s.mem + k;
+        }
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(HostBlock) * kSlabBlocks, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    try {
+        g_slabs.push_back(Slab{static_cast<HostBlock *>(p), 1u});
+    } catch (...) {
+        (void)hipHostFree(p);
+        return nullptr;
+    }
+    return g_slabs.back().mem;
+}
+
+void host_block_give(HostBlock *b)
+{
+    if (!b) return;
+    std::lock_guard<std::mutex> lk(g_slab_mu);
+    for (size_t i = 0; i < g_slabs.size(); ++i) {
+        Slab &s = g_slabs[i];
+        if (b < s.mem || b >= s.mem + kSlabBlocks) continue;
+        s.used &= ~(uint64_t(1) << (b - s.mem));
+        if (!s.used && g_slabs.size() > 1) {
+            (void)hipHostFree(s.mem);
+            g_slabs.erase(g_slabs.begin() + (ptrdiff_t)i);
+        }
+        return;
+    }
 }
 
 struct Layout {
@@ -97,6 +154,7 @@ struct soma_ctx {
     std::vector<int32_t> tile_first;   // first tile of every system, of the table made last
     int ptiles_packed = 0, ptiles_wpb = 0;   // the tiling and waves per block they were built for
     int device = 0;                    // the GPU the context was created on
+    HostBlock *host = nullptr;         // pinned; nullptr: results and status are copied
     double *scratch_dev = nullptr;     // that GPU's static scratch (soma_observables_noalloc)
     // density_mode 1 keeps the counts in rotation (base[(s+1)&1] + delta[(s+2)%3]
     // before sweep s); `rot` says the buffers are in that layout.  Otherwise
@@ -437,14 +495,26 @@ int status_error(soma_ctx *c, uint32_t st)
     return SOMA_OK;
 }
 
-// Synchronise and report latched device status bits.
-int sync_status(soma_ctx *c)
+// Where the last kernel of a call leaves the status word (see wait_status).
+soma::Report report_to(const soma_ctx *c) { return soma::Report{c->status(), c->host ? &c->host->status : nullptr}; }
+
+// Wait for the stream and report latched device status bits; `reported`: the
+// last kernel launched has stored the status word for the host.
+int wait_status(soma_ctx *c, bool reported)
 {
-    HIPCHK(c, hipStreamSynchronize(c->stream));
     uint32_t st = 0;
-    HIPCHK(c, hipMemcpy(&st, c->status(), sizeof st, hipMemcpyDeviceToHost));
+    if (c->host) {
+        if (!reported) HIPCHK(c, soma::launch_report(report_to(c), c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        st = *const_cast<volatile uint32_t *>(&c->host->status);
+    } else {
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        HIPCHK(c, hipMemcpy(&st, c->status(), sizeof st, hipMemcpyDeviceToHost));
+    }
     return status_error(c, st);
 }
+
+int sync_status(soma_ctx *c) { return wait_status(c, false); }
 
 // Launch shape of the sweep kernel: waves per workgroup, resident grid
 // (waves per compute unit, 0 for one tile per wave) and block order.
@@ -878,7 +948,8 @@ int record_sweeps(soma_ctx *c, int32_t n, hipStream_t st, hipEvent_t *ev = nullp
         HIPCHK(c, soma::launch_sweep(c->repr, c->cw, a, st));
         if (ev) HIPCHK(c, hipEventRecord(ev[3 * r + 1], st));
         if (c->density_mode == 0)
-            HIPCHK(c, soma::launch_fold(c->cw, c->counts(), c->delta(0), c->counts(), c->L.count_words, c->status(), st));
+            HIPCHK(c, soma::launch_fold(c->cw, c->counts(), c->delta(0), c->counts(), c->L.count_words, c->status(), st,
+                                        c->sweep_ctr(), r == n - 1 ? (uint32_t)n : 0u));
         if (c->density_mode == 2) {
             soma::FoldFacesArgs f{};
             f.systems = c->d_sys();
@@ -894,8 +965,13 @@ int record_sweeps(soma_ctx *c, int32_t n, hipStream_t st, hipEvent_t *ev = nullp
         if (c->density_mode == 3) HIPCHK(c, soma::launch_mirror(c->cw, mirror_args(c, (uint32_t)r), st));
         if (ev) HIPCHK(c, hipEventRecord(ev[3 * r + 2], st));
     }
-    if (c->density_mode == 3 && n > 0) HIPCHK(c, soma::launch_mirror_check(c->cw, mirror_args(c, 0), (uint32_t)n, st));
-    HIPCHK(c, soma::launch_advance(c->sweep_ctr(), (uint32_t)n, st));
+    // the sweep counter: advanced by the last fold (mode 0) or by the check of
+    // the packed counts (mode 3), else by a kernel of its own
+    if (n == 0 || c->density_mode == 0) return SOMA_OK;
+    if (c->density_mode == 3 && c->cw == soma::COUNT_U16)
+        HIPCHK(c, soma::launch_mirror_check(c->cw, mirror_args(c, 0), (uint32_t)n, c->sweep_ctr(), st));
+    else
+        HIPCHK(c, soma::launch_advance(c->sweep_ctr(), (uint32_t)n, st));
     return SOMA_OK;
 }
 
@@ -1095,10 +1171,15 @@ int observables_into(soma_ctx *c, int32_t sys, soma_obs *out, double *partials, 
     a.accept = c->accept() + (size_t)sys * soma::kAcceptSlots * soma::kAcceptStride;
     a.conv = c->conv() + 2 * (size_t)sys;
     a.status = c->status();
-    HIPCHK(c, soma::launch_observables(c->repr, c->cw, a, result, c->stream));
+    // (straight into pinned host memory where there is some)
+    HIPCHK(c, soma::launch_observables(c->repr, c->cw, a, c->host ? &c->host->obs : result, c->stream));
     soma::ObsResult r;
-    HIPCHK(c, hipMemcpyAsync(&r, result, sizeof r, hipMemcpyDeviceToHost, c->stream));
+    if (!c->host) HIPCHK(c, hipMemcpyAsync(&r, result, sizeof r, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (c->host) {
+        std::atomic_thread_fence(std::memory_order_acquire);
+        r = c->host->obs;
+    }
     if ((rc = status_error(c, r.status)) != SOMA_OK) return rc;
     const double n = (double)h.d.n_chains;
     out->Re2 = r.q[0] / n;
@@ -1168,6 +1249,7 @@ int soma_create(const soma_system_desc *sys, int32_t n_sys, const soma_options *
         c->n_cus = cus;
         c->device = dev;
         c->scratch_dev = scratch_for_device(dev);
+        c->host = host_block_take();
         c->err.reserve(kErrCapacity);
     }
     set_shape(c, c->waves_per_block, opt->waves_per_cu, opt->launch_order == 0 ? 1 : 0, opt->packed_tiles);
@@ -1232,6 +1314,7 @@ int soma_destroy(soma_ctx *c)
     if (c->ws) (void)hipStreamSynchronize(c->stream);
     drop_graphs(c);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
+    host_block_give(c->host);
     delete c;
     return SOMA_OK;
 }
@@ -1291,10 +1374,11 @@ int soma_density(soma_ctx *c, int32_t sys, uint32_t *dst, int32_t dst_on_device)
     if ((rc = canonicalize(c)) != SOMA_OK) return rc;
     const HostSys &h = c->sys[sys];
     uint32_t *target = dst_on_device ? dst : static_cast<uint32_t *>(c->staging());
-    HIPCHK(c, soma::launch_unpack_counts(c->cw, c->counts(), h.dev.cell_off, h.dev.n_cells, target, c->stream));
+    HIPCHK(c, soma::launch_unpack_counts(c->cw, c->counts(), h.dev.cell_off, h.dev.n_cells, target, report_to(c),
+                                         c->stream));
     if (!dst_on_device)
         HIPCHK(c, hipMemcpyAsync(dst, target, sizeof(uint32_t) * 2 * h.dev.n_cells, hipMemcpyDeviceToHost, c->stream));
-    return sync_status(c);
+    return wait_status(c, true);
 }
 
 int soma_fields(soma_ctx *c, int32_t sys, float *dst, int32_t dst_on_device)
@@ -1313,10 +1397,11 @@ int soma_fields(soma_ctx *c, int32_t sys, float *dst, int32_t dst_on_device)
     f.omega = c->omega();
     f.tgt = c->tgt();
     f.out = dst_on_device ? dst : static_cast<float *>(c->staging());
+    f.report = report_to(c);
     HIPCHK(c, soma::launch_fields(c->cw, f, c->stream));
     if (!dst_on_device)
         HIPCHK(c, hipMemcpyAsync(dst, f.out, sizeof(float) * 2 * h.dev.n_cells, hipMemcpyDeviceToHost, c->stream));
-    return sync_status(c);
+    return wait_status(c, true);
 }
 
 int soma_observables(soma_ctx *c, int32_t sys, soma_obs *out)

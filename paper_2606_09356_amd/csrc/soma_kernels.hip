@@ -1584,8 +1584,11 @@ __global__ __launch_bounds__(256) void k_fold_faces(FoldFacesArgs a)
 // words past the last full quadruple.
 template <int CW>
 __global__ __launch_bounds__(256) void k_fold(const uint32_t *in, uint32_t *delta, uint32_t *counts, int64_t n,
-                                              uint32_t *status)
+                                              uint32_t *status, uint64_t *ctr, uint32_t advance)
 {
+    // (the last kernel of a batch of sweeps advances the sweep counter, which
+    // no kernel of this launch reads)
+    if (advance != 0u && blockIdx.x == 0 && threadIdx.x == 0) *ctr += advance;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t n4 = n >> 2;
@@ -1664,7 +1667,8 @@ __global__ __launch_bounds__(256) void k_mirror(MirrorArgs a)
 // Running half sums of the copy blocks against (sweeps) x (beads); clears
 // them for the next batch (one block; each thread clears what it read).
 __global__ __launch_bounds__(1024) void k_mirror_check(unsigned long long *part, int n_part,
-                                                       unsigned long long expected, uint32_t *status)
+                                                       unsigned long long expected, uint32_t *status, uint64_t *ctr,
+                                                       uint32_t advance)
 {
     __shared__ unsigned long long red[16];
     unsigned long long sum = 0;
@@ -1679,6 +1683,7 @@ __global__ __launch_bounds__(1024) void k_mirror_check(unsigned long long *part,
         unsigned long long t = 0;
         for (int k = 0; k < (int)(blockDim.x >> 6); ++k) t += red[k];
         if (t != expected) atomicOr(status, ST_COUNT_OVERFLOW);
+        *ctr += advance;
     }
 }
 
@@ -1829,11 +1834,18 @@ __global__ __launch_bounds__(256) void k_state(StateArgs a)
     }
 }
 
+__device__ __forceinline__ void report_status(const Report &r)
+{
+    if (r.host && blockIdx.x == 0 && threadIdx.x == 0) *r.host = *r.status;
+}
+__global__ void k_report(Report r) { report_status(r); }
+
 // Fields of one system as float [2][M] (A then B), from its counts or its
 // frozen array.
 template <int CW>
 __global__ __launch_bounds__(256) void k_fields(FieldArgs a)
 {
+    report_status(a.report);
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= a.n_cells) return;
     const DevSys &S = a.systems[a.sys];
@@ -1860,8 +1872,9 @@ __global__ __launch_bounds__(256) void k_fields(FieldArgs a)
 // Counts of one system as uint32 [2][M].
 template <int CW>
 __global__ __launch_bounds__(256) void k_unpack_counts(const uint32_t *counts, int64_t cell_off, int64_t n_cells,
-                                                       uint32_t *out)
+                                                       uint32_t *out, Report report)
 {
+    report_status(report);
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n_cells) return;
     const uint2 n = load_counts<CW>(counts, cell_off + c);
@@ -2648,12 +2661,18 @@ hipError_t launch_fields(int cw, const FieldArgs &a, hipStream_t st)
 }
 
 hipError_t launch_unpack_counts(int cw, const uint32_t *counts, int64_t cell_off, int64_t n_cells,
-                                uint32_t *out, hipStream_t st)
+                                uint32_t *out, const Report &report, hipStream_t st)
 {
     const int blocks = (int)((n_cells + 255) / 256);
     if (blocks == 0) return hipSuccess;
-    if (cw == COUNT_U16) hipLaunchKernelGGL((k_unpack_counts<COUNT_U16>), dim3(blocks), dim3(256), 0, st, counts, cell_off, n_cells, out);
-    else hipLaunchKernelGGL((k_unpack_counts<COUNT_U32>), dim3(blocks), dim3(256), 0, st, counts, cell_off, n_cells, out);
+    if (cw == COUNT_U16) hipLaunchKernelGGL((k_unpack_counts<COUNT_U16>), dim3(blocks), dim3(256), 0, st, counts, cell_off, n_cells, out, report);
+    else hipLaunchKernelGGL((k_unpack_counts<COUNT_U32>), dim3(blocks), dim3(256), 0, st, counts, cell_off, n_cells, out, report);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(const Report &r, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(1), 0, st, r);
     return hipGetLastError();
 }
 
@@ -2682,11 +2701,11 @@ hipError_t launch_mirror(int cw, const MirrorArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_mirror_check(int cw, const MirrorArgs &a, uint32_t n_sweeps, hipStream_t st)
+hipError_t launch_mirror_check(int cw, const MirrorArgs &a, uint32_t n_sweeps, uint64_t *ctr, hipStream_t st)
 {
     if (a.count_words <= 0 || cw != COUNT_U16 || n_sweeps == 0) return hipSuccess;
     hipLaunchKernelGGL(k_mirror_check, dim3(1), dim3(1024), 0, st, a.part, (int)mirror_blocks(a.count_words),
-                       a.beads * (unsigned long long)n_sweeps, a.status);
+                       a.beads * (unsigned long long)n_sweeps, a.status, ctr, n_sweeps);
     return hipGetLastError();
 }
 
@@ -2735,15 +2754,15 @@ hipError_t launch_make_tiles(const MakeTilesArgs &a, hipStream_t st)
 }
 
 hipError_t launch_fold(int cw, const uint32_t *counts_in, uint32_t *delta, uint32_t *counts_out, int64_t n,
-                       uint32_t *status, hipStream_t st)
+                       uint32_t *status, hipStream_t st, uint64_t *ctr, uint32_t advance)
 {
     if (n <= 0) return hipSuccess;
     int64_t blocks = ((n + 3) / 4 + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     if (cw == COUNT_U16)
-        hipLaunchKernelGGL((k_fold<COUNT_U16>), dim3((unsigned)blocks), dim3(256), 0, st, counts_in, delta, counts_out, n, status);
+        hipLaunchKernelGGL((k_fold<COUNT_U16>), dim3((unsigned)blocks), dim3(256), 0, st, counts_in, delta, counts_out, n, status, ctr, advance);
     else
-        hipLaunchKernelGGL((k_fold<COUNT_U32>), dim3((unsigned)blocks), dim3(256), 0, st, counts_in, delta, counts_out, n, status);
+        hipLaunchKernelGGL((k_fold<COUNT_U32>), dim3((unsigned)blocks), dim3(256), 0, st, counts_in, delta, counts_out, n, status, ctr, advance);
     return hipGetLastError();
 }
 

@@ -122,6 +122,15 @@ struct ReorderArgs {
     uint32_t *status;
 };
 
+// The status word, for the host: a kernel that is the last of its call stores
+// it (as it was before that kernel) into pinned host memory, which the host
+// reads after the stream has been waited for.  Null: nothing to report.
+struct Report {
+    const uint32_t *status;
+    uint32_t *host;
+};
+hipError_t launch_report(const Report &r, hipStream_t st);
+
 struct FieldArgs {
     const DevSys *systems;
     int sys;
@@ -130,6 +139,7 @@ struct FieldArgs {
     const float2 *omega;
     const float2 *tgt;             // umbrella targets
     float *out;                    // [2][n_cells]
+    Report report;
 };
 
 struct InitArgs {
@@ -231,7 +241,7 @@ hipError_t launch_acc_fold(const Tile *tiles, int n_tiles, unsigned long long *a
 hipError_t launch_density(int repr, int cw, const DensityArgs &a, hipStream_t st);
 hipError_t launch_fields(int cw, const FieldArgs &a, hipStream_t st);
 hipError_t launch_unpack_counts(int cw, const uint32_t *counts, int64_t cell_off, int64_t n_cells,
-                                uint32_t *out, hipStream_t st);
+                                uint32_t *out, const Report &report, hipStream_t st);
 // Density mode 2: the fold of one sweep's face fluxes, one block per chunk
 // of kFoldChunk cells of one system.
 constexpr int kFoldChunk = 2048;
@@ -252,7 +262,7 @@ struct FoldFacesArgs {
 };
 hipError_t launch_fold_faces(int cw, const FoldFacesArgs &a, int n_chunks, hipStream_t st);
 hipError_t launch_fold(int cw, const uint32_t *counts_in, uint32_t *delta, uint32_t *counts_out, int64_t n,
-                       uint32_t *status, hipStream_t st);
+                       uint32_t *status, hipStream_t st, uint64_t *ctr = nullptr, uint32_t advance = 0);
 // Density mode 3: after sweep s, copy base[(s+1) mod 2] (the counts the
 // sweep's atomics produced) into base[s mod 2]; for packed 16-bit counts
 // also check that the halves sum to the number of beads: each copy block
@@ -271,8 +281,9 @@ struct MirrorArgs {
     uint32_t *status;
 };
 hipError_t launch_mirror(int cw, const MirrorArgs &a, hipStream_t st);
-// After n_sweeps mirrors of a batch (packed 16-bit counts only).
-hipError_t launch_mirror_check(int cw, const MirrorArgs &a, uint32_t n_sweeps, hipStream_t st);
+// After n_sweeps mirrors of a batch (packed 16-bit counts only); advances the
+// sweep counter by as much.
+hipError_t launch_mirror_check(int cw, const MirrorArgs &a, uint32_t n_sweeps, uint64_t *ctr, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_advance(uint64_t *ctr, uint32_t n, hipStream_t st);
 hipError_t launch_init(const InitArgs &a, hipStream_t st);
