@@ -113,7 +113,7 @@ struct Layout {
     size_t systems, tiles, chain_id, chain_id2, P[3], C[3], Q[3], D[3], keys, hist, bsum, perm, base, delta, flux, chunks,
         omega, accept, status, partials, obs_out, staging, chain_class, chain_class2, conv, tgt, place_W, place_bsum,
         ptiles, tile_first, total;   // base: counts, delta: density delta; ptiles: block tiles
-    int64_t total_slots = 0, total_cells = 0, total_chains = 0, count_words = 0, total_beads = 0;
+    int64_t total_slots = 0, total_cells = 0, total_chains = 0, count_words = 0, total_beads = 0, total_blocks = 0;
     int n_tiles = 0;
     int n_ptiles_cap = 0;   // entries of the block/stream tile table
     int n_chunks = 0;      // fold chunks of density mode 2
@@ -330,7 +330,7 @@ void set_field_coefs(HostSys &h);
 Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt, std::vector<HostSys> *out)
 {
     Layout L{};
-    int64_t slots = 0, cells = 0, chains = 0, beads = 0, stiles = 0;
+    int64_t slots = 0, cells = 0, chains = 0, beads = 0, stiles = 0, blocks = 0;
     int tiles = 0;
     int64_t max_cells = 1;
     for (int32_t k = 0; k < n_sys; ++k) {
@@ -381,6 +381,9 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
             v.delta = (float)d.move_halfwidth;
             v.inv_P = (float)(1.0 / P);
             v.n_cells = M;
+            v.blk_off = blocks;
+            v.nb1 = (int32_t)soma::sort_blocks(d.grid[1]);
+            v.nb2 = (int32_t)soma::sort_blocks(d.grid[2]);
             v.umb = 0;
             v.walls = (d.walls[0] != 0 || d.walls[1] != 0) ? 1 : 0;
             v.wall_lo = d.walls[0];
@@ -402,6 +405,7 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
         }
         slots = align64(slots + (int64_t)d.n_chains * 2 * P);
         cells = align64(cells + M);
+        blocks += soma::sort_blocks(d.grid[0]) * soma::sort_blocks(d.grid[1]) * soma::sort_blocks(d.grid[2]);
         chains += d.n_chains;
         beads += (int64_t)d.n_chains * d.N;
         tiles += nt;
@@ -411,6 +415,7 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     const bool cell = opt->pos_repr == SOMA_POS_CELL_F32;
     L.total_slots = slots;
     L.total_cells = cells;
+    L.total_blocks = blocks;
     L.total_chains = chains;
     L.total_beads = beads;
     L.n_tiles = tiles;
@@ -432,8 +437,8 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     for (int a = 0; a < 3; ++a) L.Q[a] = take(sizeof(float) * slots);
     for (int a = 0; a < 3; ++a) L.D[a] = cell ? take(sizeof(int) * slots) : 0;
     L.keys = take(sizeof(uint32_t) * chains);
-    L.hist = take(sizeof(uint32_t) * cells);
-    L.bsum = take(sizeof(uint32_t) * soma::reorder_bsum_words(cells));
+    L.hist = take(sizeof(uint32_t) * blocks);
+    L.bsum = take(sizeof(uint32_t) * soma::reorder_bsum_words(blocks));
     L.perm = take(sizeof(uint32_t) * chains);
     L.base = take(sizeof(uint32_t) * 2 * L.count_words);
     L.delta = take(sizeof(uint32_t) * 3 * L.count_words);
@@ -891,7 +896,7 @@ soma::ReorderArgs reorder_args(const soma_ctx *c)
     r.tiles = c->d_tiles();
     r.n_tiles = c->L.n_tiles;
     r.total_chains = c->L.total_chains;
-    r.total_cells = c->L.total_cells;
+    r.total_blocks = c->L.total_blocks;
     for (int d = 0; d < 3; ++d) {
         (&r.P0)[d] = c->P(d);
         (&r.C0)[d] = c->C(d);
@@ -908,7 +913,7 @@ soma::ReorderArgs reorder_args(const soma_ctx *c)
     return r;
 }
 
-// Sort the chains of every system by the cell of their first bead and move
+// Sort the chains of every system by the cell block of their middle bead and move
 // positions and logical ids into that order (eager launches, never captured).
 int reorder_chains(soma_ctx *c)
 {

@@ -705,15 +705,18 @@ struct Head {
     uint32_t rel;
     const uint32_t *chain_id;
     PosArrays pos;
+    const uint2 *halo;         // stream tiles only
+    int64_t halo_cap;
 };
-__device__ __forceinline__ Head head_of(ArgPtr a, bool cells)
+__device__ __forceinline__ Head head_of(ArgPtr a, bool cells, bool stream)
 {
     Head h{a->wtiles, a->sweep_ctr, a->systems, a->acc_tile, a->n_wtiles, a->waves_per_block, a->remap_blocks, a->rel,
-           a->chain_id, pos_arrays(a)};
+           a->chain_id, pos_arrays(a), a->halo, a->halo_cap};
     asm volatile("" : "+s"(h.tiles), "+s"(h.ctr), "+s"(h.systems), "+s"(h.acc_tile), "+s"(h.n_tiles),
                       "+s"(h.waves_per_block), "+s"(h.remap), "+s"(h.rel), "+s"(h.chain_id), "+s"(h.pos.P0),
                       "+s"(h.pos.P1), "+s"(h.pos.P2));
     if (cells) asm volatile("" : "+s"(h.pos.C0), "+s"(h.pos.C1), "+s"(h.pos.C2));
+    if (stream) asm volatile("" : "+s"(h.halo), "+s"(h.halo_cap));
     return h;
 }
 
@@ -764,8 +767,14 @@ __device__ __forceinline__ TileLane lane_of(const Tile &T)
     // the FP32 error of the product (q < 1024)
     L.g = (int)(((float)q + 0.5f) * T.inv_P);
     L.p = q - L.g * P;
-    L.valid = lane < n && (TIL != TIL_STREAM || lane > 0 || (T.lanes >> 18 & 1u));
-    L.own = TIL == TIL_STREAM ? lane >= 1 && lane <= kStreamLanes && lane < n : L.valid;
+    if constexpr (TIL == TIL_STREAM) {
+        // (single unsigned comparisons; n is at least 2)
+        const uint32_t first = 1u - (T.lanes >> 18 & 1u), end = (uint32_t)min(n, kStreamLanes + 1);
+        L.valid = (uint32_t)lane - first < (uint32_t)n - first;
+        L.own = (uint32_t)lane - 1u < end - 1u;
+    } else {
+        L.valid = L.own = lane < n;
+    }
     return L;
 }
 
@@ -897,7 +906,7 @@ __device__ __forceinline__ void tile_load(ArgPtr a, const Head &h, const Tile &T
     clog = ld_off<uint32_t>(h.chain_id + T.chain, (uint32_t)(L.valid ? L.g : back) << 2);
     const uint32_t lane = (uint32_t)tile_lane<TIL>();
     if (TIL == TIL_STREAM && L.valid && !L.own) {
-        const uint2 *e = a->halo + halo_index((int)(s & 1), 0, tile, 0, a->halo_cap);
+        const uint2 *e = h.halo + halo_index((int)(s & 1), 0, tile, 0, h.halo_cap);
         // tile - 1, side 1 for lane 0; tile + 1, side 0 for lane 63
         halo_get(e - kHaloSlots, lane == 0 ? 0u : 3u * kHaloSide, b0, b1);
     } else {
@@ -1413,7 +1422,7 @@ __device__ __forceinline__ void sweep_body(ArgPtr a)
 {
     using Bead = typename std::conditional<R == REPR_F32, BeadF32, BeadCell>::type;
     constexpr bool FI = DM == 1;
-    const Head h = head_of(a, R == REPR_CELL);
+    const Head h = head_of(a, R == REPR_CELL, TIL == TIL_STREAM);
     // (wave-uniform; readfirstlane lets the tables be read with scalar loads)
     const int bid = block_index(h.remap);
     const int wave = __builtin_amdgcn_readfirstlane(
@@ -1891,11 +1900,17 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *p, int64_t n, uint32
 __global__ void k_advance(uint64_t *ctr, uint32_t n) { *ctr += n; }
 
 // ---------------------------------------------------------------------------
-// Spatial chain reorder: chains are sorted by the cell of their first bead
-// (a counting sort over the context-wide cell index, which keeps every system
-// inside its own chain range), so that the waves of one XCD work on a compact
-// slab whose counts stay in that XCD's L2.  Logical chain ids move with the
-// chains, so the sweep's results do not change.
+// Spatial chain reorder: a counting sort of the chains by the block of 4 x 4
+// x 4 cells that holds their middle bead (blocks in linear order, context-wide,
+// so every system stays inside its own chain range), so that the chains of a
+// wave share count lines and the waves in flight work on a compact region.
+// Logical chain ids move with the chains, so the sweep's results do not change.
+// (A block, not a cell: at two beads per cell a row of cells in z holds one
+// chain of 32 beads per 16 cells, so consecutive chains of a sort by cell are
+// 16 cells apart, those of a sort by block are in the same block.  The middle
+// bead: it is nearest to the others.  Distinct 64-byte count lines that a wave
+// of such chains updates: 0.184 per bead by cell of the first bead, 0.159 by
+// block of the middle bead; and the histogram is 64 times smaller.)
 // ---------------------------------------------------------------------------
 template <int R>
 __global__ __launch_bounds__(256) void k_reorder_keys(ReorderArgs a)
@@ -1907,13 +1922,14 @@ __global__ __launch_bounds__(256) void k_reorder_keys(ReorderArgs a)
     const SysPtr S = sys_at(a.systems, T.sys);
     const SysView v = make_view(S);
     const TileLane L = lane_of<TIL_WAVE>(T);
-    if (!L.valid || L.p != 0) return;
+    if (!L.valid || L.p != (int)(T.lanes >> 12 & 63u)) return;      // lane P / 2 of its chain
     Bead b[2];
     load_pair(pos_arrays(a), T.slot, (uint32_t)tile_lane<TIL_WAVE>() * 8u, b[0], b[1]);
     CellPos c[1];
-    const Bead first[1] = {b[0]};
-    cells_of<1>(first, v, S, false, a.status, c);
-    const uint32_t key = (uint32_t)(S->cell_off + lin(c[0], v));
+    const Bead mid[1] = {b[0]};
+    cells_of<1>(mid, v, S, false, a.status, c);
+    const int64_t blk = ((int64_t)(c[0].x / kSortBlock) * S->nb1 + c[0].y / kSortBlock) * S->nb2 + c[0].z / kSortBlock;
+    const uint32_t key = (uint32_t)(S->blk_off + blk);
     a.keys[T.chain + L.g] = key;
     atomicAdd(a.hist + key, 1u);
 }
@@ -2793,14 +2809,14 @@ hipError_t launch_reorder(int repr, const ReorderArgs &a, hipStream_t st)
 {
     const int tblocks = (a.n_tiles + 3) / 4;
     if (tblocks == 0) return hipSuccess;
-    hipError_t e = launch_fill_u32(a.hist, a.total_cells, 0u, st);
+    hipError_t e = launch_fill_u32(a.hist, a.total_blocks, 0u, st);
     if (e != hipSuccess) return e;
     if (repr == REPR_F32) hipLaunchKernelGGL((k_reorder_keys<REPR_F32>), dim3(tblocks), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_reorder_keys<REPR_CELL>), dim3(tblocks), dim3(256), 0, st, a);
-    const int nb = (int)((a.total_cells + kScanTile - 1) / kScanTile);
-    hipLaunchKernelGGL(k_scan_partials, dim3(nb), dim3(kScanBlock), 0, st, a.hist, a.total_cells, a.bsum);
+    const int nb = (int)((a.total_blocks + kScanTile - 1) / kScanTile);
+    hipLaunchKernelGGL(k_scan_partials, dim3(nb), dim3(kScanBlock), 0, st, a.hist, a.total_blocks, a.bsum);
     hipLaunchKernelGGL(k_scan_bsum, dim3(1), dim3(kScanBlock), 0, st, a.bsum, nb);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kScanBlock), 0, st, a.hist, a.total_cells, a.bsum);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kScanBlock), 0, st, a.hist, a.total_blocks, a.bsum);
     const int cblocks = (int)((a.total_chains + 255) / 256);
     hipLaunchKernelGGL(k_reorder_scatter, dim3(cblocks), dim3(256), 0, st, a);
     if (repr == REPR_F32) hipLaunchKernelGGL((k_reorder_permute<REPR_F32>), dim3(tblocks), dim3(256), 0, st, a);
@@ -2808,7 +2824,7 @@ hipError_t launch_reorder(int repr, const ReorderArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-int64_t reorder_bsum_words(int64_t total_cells) { return (total_cells + kScanTile - 1) / kScanTile; }
+int64_t reorder_bsum_words(int64_t total_blocks) { return (total_blocks + kScanTile - 1) / kScanTile; }
 
 hipError_t launch_init(const InitArgs &a, hipStream_t st)
 {

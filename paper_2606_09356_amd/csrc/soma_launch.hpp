@@ -25,6 +25,8 @@ struct SweepArgs {
     const uint32_t *chain_id;      // logical chain id (within its system) per chain slot
     float *P0, *P1, *P2;           // coordinates (F32) or offsets (CELL)
     int *C0, *C1, *C2;             // cells (CELL only)
+    uint2 *halo;                   // stream tiles: boundary bead pairs, see halo_index
+    int64_t halo_cap;              // stream tile entries per halo array
     const Tile *tiles;
     int n_tiles;
     const Tile *ptiles;            // block tiles (chains packed over the waves of a block)
@@ -51,8 +53,6 @@ struct SweepArgs {
     uint8_t *chain_class;          // per logical chain: 0 = pattern a, 1 = pattern b
     const float2 *tgt;             // umbrella target (phi_A, phi_B) per cell
     unsigned long long *conv;      // [n_sys][2]: chains converted to class a, to class b
-    uint2 *halo;                   // stream tiles: boundary bead pairs, see halo_index
-    int64_t halo_cap;              // stream tile entries per halo array
 };
 
 // The one-tile-per-wave kernels for uniform moves without coupling (wave
@@ -109,14 +109,14 @@ struct ReorderArgs {
     const DevSys *systems;
     const Tile *tiles;
     int n_tiles;
-    int64_t total_chains, total_cells;
+    int64_t total_chains, total_blocks;
     float *P0, *P1, *P2;           // live positions
     int *C0, *C1, *C2;
     float *Q0, *Q1, *Q2;           // scratch positions (same layout)
     int *D0, *D1, *D2;
     uint32_t *chain_id, *chain_id2;
-    uint32_t *keys;                // per chain: context-wide cell of bead 0
-    uint32_t *hist;                // per cell: count, then exclusive offsets
+    uint32_t *keys;                // per chain: context-wide block of its middle bead
+    uint32_t *hist;                // per block: count, then exclusive offsets
     uint32_t *bsum;                // scan block sums
     uint32_t *perm;                // perm[new] = old
     uint32_t *status;
@@ -289,7 +289,7 @@ hipError_t launch_advance(uint64_t *ctr, uint32_t n, hipStream_t st);
 hipError_t launch_init(const InitArgs &a, hipStream_t st);
 hipError_t launch_iota_chains(const ReorderArgs &a, hipStream_t st);
 hipError_t launch_reorder(int repr, const ReorderArgs &a, hipStream_t st);
-int64_t reorder_bsum_words(int64_t total_cells);
+int64_t reorder_bsum_words(int64_t total_blocks);
 hipError_t launch_observables(int repr, int cw, const ObsArgs &a, ObsResult *out, hipStream_t st);
 hipError_t launch_place(const PlaceArgs &a, unsigned long long *scan_bsum, hipStream_t st);
 int64_t place_bsum_words(int64_t n_cells);

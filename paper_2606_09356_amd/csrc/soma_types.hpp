@@ -33,6 +33,11 @@ enum StatusBits : uint32_t {
 enum StateBits : uint32_t { ST_BAD_VALUE = 1u, ST_BAD_OFFSET = 2u, ST_BAD_CELL = 4u, ST_BAD_WALL = 8u };
 constexpr int kStateCellLimit = 1 << 22;   // |cell| of a state set from the host stays below this
 
+// The reorder sorts chains by the block of kSortBlock^3 cells of their middle
+// bead.
+constexpr int kSortBlock = 4;
+__host__ __device__ inline int64_t sort_blocks(int n) { return (n + kSortBlock - 1) / kSortBlock; }
+
 // Attempts of the initial walks and of the placement to draw a chain that
 // fits between walls.
 constexpr int kMaxAttempts = 64;
@@ -61,6 +66,9 @@ struct alignas(16) DevSys {
     // omega_A = c_same nA + c_other nB + c0, omega_B = c_other nA + c_same nB + c0
     float c_same, c_other, c0;
     int64_t n_cells;
+    // chain reorder: blocks of kSortBlock^3 cells
+    int64_t blk_off;       // first block of the system (context-wide)
+    int32_t nb1, nb2;      // blocks along y and z
     // bond-force-biased moves (smc != 0): displacement A F + sqrt(2A) xi in
     // FP64, rejected at 0.99 cell edges; the acceptance ratio in FP32
     int32_t smc;
