@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <new>
@@ -327,9 +328,30 @@ int validate(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt
 
 void set_field_coefs(HostSys &h);
 
+// Stored cells of a grid in bricks (ragged edges padded to 4 in y and z).
+int64_t brick_cells(const int32_t *n) { return (int64_t)n[0] * ((n[1] + 3) & ~3) * ((n[2] + 3) & ~3); }
+
+// A system's cells are stored in bricks unless the padding would add more
+// than half (grids of a few cells, whose counts fit one cache anyway, and
+// whose copies and folds would grow); never if the context's count words,
+// bounded by 2^30 without padding, would pass that bound with it.
+bool in_bricks(const int32_t *n, bool allowed)
+{
+    return allowed && 2 * brick_cells(n) <= 3 * ((int64_t)n[0] * n[1] * n[2]);
+}
+
 Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt, std::vector<HostSys> *out)
 {
     Layout L{};
+    bool bricks = true;
+    {
+        int64_t words = 0;
+        for (int32_t k = 0; k < n_sys; ++k) {
+            const int32_t *n = sys[k].grid;
+            words += align64(in_bricks(n, true) ? brick_cells(n) : (int64_t)n[0] * n[1] * n[2]);
+        }
+        bricks = words * (opt->count_width == SOMA_COUNT_U16 ? 1 : 2) < (int64_t(1) << 30);
+    }
     int64_t slots = 0, cells = 0, chains = 0, beads = 0, stiles = 0, blocks = 0;
     int tiles = 0;
     int64_t max_cells = 1;
@@ -338,6 +360,8 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
         const int P = (d.N + 1) / 2, G = soma::kWave / P;
         const int64_t M = (int64_t)d.grid[0] * d.grid[1] * d.grid[2];
         const int nt = (d.n_chains + G - 1) / G;
+        const bool brick = in_bricks(d.grid, bricks);
+        const int64_t stored = brick ? brick_cells(d.grid) : M;
         if (out) {
             HostSys h{};
             h.d = d;
@@ -381,6 +405,15 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
             v.delta = (float)d.move_halfwidth;
             v.inv_P = (float)(1.0 / P);
             v.n_cells = M;
+            v.brick_shift = brick ? 2 : 0;
+            v.brick_mask = brick ? 3 : 0;
+            v.B1 = brick ? (d.grid[1] + 3) / 4 : d.grid[1];
+            v.B2 = brick ? (d.grid[2] + 3) / 4 : d.grid[2];
+            v.n_store = stored;
+            v.r_n1 = 1.0 / d.grid[1];
+            v.r_n2 = 1.0 / d.grid[2];
+            v.r_B1 = 1.0 / v.B1;
+            v.r_B2 = 1.0 / v.B2;
             v.blk_off = blocks;
             v.nb1 = (int32_t)soma::sort_blocks(d.grid[1]);
             v.nb2 = (int32_t)soma::sort_blocks(d.grid[2]);
@@ -404,7 +437,7 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
             out->push_back(std::move(h));
         }
         slots = align64(slots + (int64_t)d.n_chains * 2 * P);
-        cells = align64(cells + M);
+        cells = align64(cells + stored);
         blocks += soma::sort_blocks(d.grid[0]) * soma::sort_blocks(d.grid[1]) * soma::sort_blocks(d.grid[2]);
         chains += d.n_chains;
         beads += (int64_t)d.n_chains * d.N;
@@ -446,7 +479,8 @@ Layout plan(const soma_system_desc *sys, int32_t n_sys, const soma_options *opt,
     {
         int64_t nch = 0;
         for (int32_t k = 0; k < n_sys; ++k) {
-            const int64_t M = (int64_t)sys[k].grid[0] * sys[k].grid[1] * sys[k].grid[2];
+            const int32_t *n = sys[k].grid;
+            const int64_t M = in_bricks(n, bricks) ? brick_cells(n) : (int64_t)n[0] * n[1] * n[2];
             nch += (M + soma::kFoldChunk - 1) / soma::kFoldChunk;
         }
         L.n_chunks = (int)nch;
@@ -793,7 +827,7 @@ int rebuild_density(soma_ctx *c, int32_t sys)
         HIPCHK(c, soma::launch_fill_u32(cur, c->L.count_words, 0u, c->stream));
     } else {
         const HostSys &h = c->sys[sys];
-        HIPCHK(c, soma::launch_fill_u32(cur + h.dev.cell_off * wpc, h.dev.n_cells * wpc, 0u, c->stream));
+        HIPCHK(c, soma::launch_fill_u32(cur + h.dev.cell_off * wpc, h.dev.n_store * wpc, 0u, c->stream));
         tb = h.tile_begin;
         te = h.tile_end;
     }
@@ -881,6 +915,26 @@ bool inside_walls(const HostSys &h, const std::vector<int> &zc)
     for (int v : zc)
         if (v < h.dev.wall_lo || v >= h.dev.wall_hi) return false;
     return true;
+}
+
+// Copy two host arrays [2][n_cells] in linear order to the pairs of the
+// system at dst (omega or targets), in the stored order.
+int store_pairs(soma_ctx *c, int32_t sys, const float *v, float2 *dst)
+{
+    const HostSys &h = c->sys[sys];
+    float *lin = static_cast<float *>(c->staging());
+    HIPCHK(c, hipMemcpyAsync(lin, v, sizeof(float) * 2 * (size_t)h.dev.n_cells, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, soma::launch_store_pairs(c->d_sys() + sys, h.dev.n_cells, lin, dst + h.dev.cell_off, c->stream));
+    return SOMA_OK;
+}
+
+// Every value of v[0, n) in [lo, hi] (false for a NaN); no early exit, so the
+// loop vectorises.
+bool all_within(const float *v, int64_t n, float lo, float hi)
+{
+    unsigned bad = 0;
+    for (int64_t i = 0; i < n; ++i) bad |= (unsigned)!(v[i] >= lo) | (unsigned)!(v[i] <= hi);
+    return bad == 0;
 }
 
 int upload_sys(soma_ctx *c, int32_t sys)
@@ -1163,8 +1217,9 @@ int observables_into(soma_ctx *c, int32_t sys, soma_obs *out, double *partials, 
     }
     a.k_half = 1.5 * (h.d.N - 1) / (h.d.Re * h.d.Re);
     a.counts = c->counts();
+    a.sys = c->d_sys() + sys;
     a.cell_off = h.dev.cell_off;
-    a.n_cells = h.dev.n_cells;
+    a.n_store = h.dev.n_store;
     const double B = (double)h.d.n_chains * h.d.N;
     a.phi_per_count = (double)h.dev.n_cells / B;
     a.chiN = h.d.chiN;
@@ -1270,7 +1325,7 @@ int soma_create(const soma_system_desc *sys, int32_t n_sys, const soma_options *
     if (n_tiles != c->L.n_tiles) return bail(fail(c, SOMA_EDEVICE, "tile table size"));
     std::vector<soma::FoldChunk> chunks;
     for (size_t k = 0; k < c->sys.size(); ++k)
-        for (int64_t f = 0; f < c->sys[k].dev.n_cells; f += soma::kFoldChunk)
+        for (int64_t f = 0; f < c->sys[k].dev.n_store; f += soma::kFoldChunk)
             chunks.push_back(soma::FoldChunk{(uint32_t)k, 0u, f});
     if ((int)chunks.size() != c->L.n_chunks) return bail(fail(c, SOMA_EDEVICE, "fold chunk table size"));
     if (!chunks.empty() &&
@@ -1379,8 +1434,8 @@ int soma_density(soma_ctx *c, int32_t sys, uint32_t *dst, int32_t dst_on_device)
     if ((rc = canonicalize(c)) != SOMA_OK) return rc;
     const HostSys &h = c->sys[sys];
     uint32_t *target = dst_on_device ? dst : static_cast<uint32_t *>(c->staging());
-    HIPCHK(c, soma::launch_unpack_counts(c->cw, c->counts(), h.dev.cell_off, h.dev.n_cells, target, report_to(c),
-                                         c->stream));
+    const soma::UnpackArgs u{c->d_sys() + sys, c->counts(), h.dev.cell_off, h.dev.n_cells, h.dev.n_store, target, report_to(c)};
+    HIPCHK(c, soma::launch_unpack_counts(c->cw, u, c->stream));
     if (!dst_on_device)
         HIPCHK(c, hipMemcpyAsync(dst, target, sizeof(uint32_t) * 2 * h.dev.n_cells, hipMemcpyDeviceToHost, c->stream));
     return wait_status(c, true);
@@ -1398,6 +1453,7 @@ int soma_fields(soma_ctx *c, int32_t sys, float *dst, int32_t dst_on_device)
     f.systems = c->d_sys();
     f.sys = sys;
     f.n_cells = h.dev.n_cells;
+    f.n_store = h.dev.n_store;
     f.counts = c->counts();
     f.omega = c->omega();
     f.tgt = c->tgt();
@@ -1539,12 +1595,9 @@ int soma_set_fields(soma_ctx *c, int32_t sys, const float *omega)
     if (!omega) return fail(c, SOMA_EINVAL, "omega is null");
     HostSys &h = c->sys[sys];
     const int64_t M = h.dev.n_cells;
-    std::vector<float2> w((size_t)M);
-    for (int64_t i = 0; i < M; ++i) {
-        if (!std::isfinite(omega[i]) || !std::isfinite(omega[M + i])) return fail(c, SOMA_ENONFINITE, "omega has a non-finite value");
-        w[(size_t)i] = make_float2(omega[i], omega[M + i]);
-    }
-    HIPCHK(c, hipMemcpyAsync(c->omega() + h.dev.cell_off, w.data(), sizeof(float2) * M, hipMemcpyHostToDevice, c->stream));
+    if (!all_within(omega, 2 * M, -std::numeric_limits<float>::max(), std::numeric_limits<float>::max()))
+        return fail(c, SOMA_ENONFINITE, "omega has a non-finite value");
+    if ((rc = store_pairs(c, sys, omega, c->omega())) != SOMA_OK) return rc;
     h.dev.frozen = 1;
     if ((rc = upload_sys(c, sys)) != SOMA_OK) return rc;
     return sync_status(c);
@@ -1569,13 +1622,8 @@ int soma_place_from_fields(soma_ctx *c, int32_t sys, const float *phi)
     if (!c->tgt()) return fail(c, SOMA_EINVAL, "the context was created without the coupling workspace (opts.coupling)");
     HostSys &h = c->sys[sys];
     const int64_t M = h.dev.n_cells;
-    std::vector<float2> t((size_t)M);
-    for (int64_t i = 0; i < M; ++i) {
-        const float a = phi[i], b = phi[M + i];
-        if (!(a >= 0.0f && a <= 4096.0f && b >= 0.0f && b <= 4096.0f))
-            return fail(c, SOMA_EINVAL, "target fields must be finite and in [0, 4096]");
-        t[(size_t)i] = make_float2(a, b);
-    }
+    if (!all_within(phi, 2 * M, 0.0f, 4096.0f))
+        return fail(c, SOMA_EINVAL, "target fields must be finite and in [0, 4096]");
     // classes with chains need weight somewhere (the integer weights of the kernels)
     int na_k[2] = {0, 0};
     for (int k = 0; k < 2; ++k) {
@@ -1585,7 +1633,7 @@ int soma_place_from_fields(soma_ctx *c, int32_t sys, const float *phi)
         const double fa = (double)na / (double)h.d.N, fb = (double)(h.d.N - na) / (double)h.d.N;
         bool any = false;
         for (int64_t i = 0; i < M && !any; ++i)
-            any = std::floor(1048576.0 * (fa * (double)t[(size_t)i].x + fb * (double)t[(size_t)i].y) + 0.5) > 0.0;
+            any = std::floor(1048576.0 * (fa * (double)phi[i] + fb * (double)phi[M + i]) + 0.5) > 0.0;
         na_k[k] = na;
         h.cls_weight[k] = any;
     }
@@ -1594,8 +1642,7 @@ int soma_place_from_fields(soma_ctx *c, int32_t sys, const float *phi)
     for (uint8_t v : cls)
         if (!h.cls_weight[v]) return fail(c, SOMA_EINVAL, "a chain class has no target weight anywhere");
     if ((rc = canonicalize(c)) != SOMA_OK) return rc;
-    HIPCHK(c, hipMemcpyAsync(c->tgt() + h.dev.cell_off, t.data(), sizeof(float2) * (size_t)M, hipMemcpyHostToDevice,
-                             c->stream));
+    if ((rc = store_pairs(c, sys, phi, c->tgt())) != SOMA_OK) return rc;
     soma::PlaceArgs pa{};
     pa.ia = init_args(c, h);
     pa.sys = c->d_sys() + sys;

@@ -134,7 +134,7 @@ hipError_t launch_report(const Report &r, hipStream_t st);
 struct FieldArgs {
     const DevSys *systems;
     int sys;
-    int64_t n_cells;
+    int64_t n_cells, n_store;
     const uint32_t *counts;        // current counts
     const float2 *omega;
     const float2 *tgt;             // umbrella targets
@@ -180,8 +180,9 @@ struct ObsArgs {
     double k_half;
     float *P0, *P1, *P2;
     int *C0, *C1, *C2;
+    const DevSys *sys;             // the system's table entry
     const uint32_t *counts;        // current counts
-    int64_t cell_off, n_cells;
+    int64_t cell_off, n_store;
     double phi_per_count;          // M / B
     double chiN, kappaN;
     int ham_form;
@@ -240,15 +241,23 @@ hipError_t launch_acc_fold(const Tile *tiles, int n_tiles, unsigned long long *a
                            unsigned long long *accept, hipStream_t st);
 hipError_t launch_density(int repr, int cw, const DensityArgs &a, hipStream_t st);
 hipError_t launch_fields(int cw, const FieldArgs &a, hipStream_t st);
-hipError_t launch_unpack_counts(int cw, const uint32_t *counts, int64_t cell_off, int64_t n_cells,
-                                uint32_t *out, const Report &report, hipStream_t st);
+struct UnpackArgs {
+    const DevSys *sys;             // the system's table entry
+    const uint32_t *counts;
+    int64_t cell_off, n_cells, n_store;
+    uint32_t *out;                 // [2][n_cells], linear order
+    Report report;
+};
+hipError_t launch_unpack_counts(int cw, const UnpackArgs &a, hipStream_t st);
+// [2][n_cells] values in linear order to pairs in the stored order.
+hipError_t launch_store_pairs(const DevSys *sys, int64_t n_cells, const float *in, float2 *out, hipStream_t st);
 // Density mode 2: the fold of one sweep's face fluxes, one block per chunk
-// of kFoldChunk cells of one system.
+// of kFoldChunk stored cells of one system.
 constexpr int kFoldChunk = 2048;
 struct FoldChunk {
     uint32_t sys;                  // index into the system table
     uint32_t pad;
-    int64_t first;                 // first cell of the chunk within its system
+    int64_t first;                 // first stored cell of the chunk within its system
 };
 struct FoldFacesArgs {
     const DevSys *systems;

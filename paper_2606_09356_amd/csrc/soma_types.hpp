@@ -66,6 +66,16 @@ struct alignas(16) DevSys {
     // omega_A = c_same nA + c_other nB + c0, omega_B = c_other nA + c_same nB + c0
     float c_same, c_other, c0;
     int64_t n_cells;
+    // Storage order of the cells (counts, fluxes, frozen fields, targets):
+    // bricks of 4 x 4 cells in y and z, a brick's 16 cells consecutive (one
+    // 64-byte line of packed counts), bricks in the linear order of their
+    // grid, whose ragged edges are padded; or, with brick_shift 0, the linear
+    // order (x * ny + y) * nz + z itself.
+    int32_t brick_shift;   // 2 or 0
+    int32_t brick_mask;    // (1 << brick_shift) - 1
+    int32_t B1, B2;        // bricks (cells) along y and z
+    int64_t n_store;       // stored cells, padding included
+    double r_n1, r_n2, r_B1, r_B2;   // reciprocals of n[1], n[2], B1, B2
     // chain reorder: blocks of kSortBlock^3 cells
     int64_t blk_off;       // first block of the system (context-wide)
     int32_t nb1, nb2;      // blocks along y and z
@@ -93,6 +103,13 @@ struct alignas(16) DevSys {
     alignas(16) uint32_t pat_a[kPatternWords];   // bit i: type of bead i (0 = A, 1 = B)
     alignas(16) uint32_t pat_b[kPatternWords];
 };
+
+// Stored index of cell (x, y, z).
+__host__ __device__ inline int64_t stored_cell(const DevSys &S, int x, int y, int z)
+{
+    const int64_t b = ((int64_t)x * S.B1 + (y >> S.brick_shift)) * S.B2 + (z >> S.brick_shift);
+    return (b << 2 * S.brick_shift) + ((y & S.brick_mask) << S.brick_shift) + (z & S.brick_mask);
+}
 
 // One tile of the sweep (wave, block or stream tile): everything a wave needs
 // to address its beads, so that the position loads go out one scalar load
