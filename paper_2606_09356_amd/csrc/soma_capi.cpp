@@ -684,6 +684,9 @@ soma::SweepArgs sweep_args(const soma_ctx *c, uint32_t rel)
     a.waves_per_block = c->waves_per_block;
     a.max_blocks = c->max_blocks;
     a.xcd_remap = c->xcd_remap;
+    a.n_systems = (int)c->sys.size();
+    a.sys0_P = c->sys[0].dev.P;
+    a.sys0_chains = c->sys[0].d.n_chains;
     a.chain_id = c->chain_id();
     for (int d = 0; d < 3; ++d) {
         (&a.P0)[d] = c->P(d);
@@ -1176,7 +1179,9 @@ int run_sweeps(soma_ctx *c, int32_t n, hipEvent_t *ev)
         int32_t seg = left;
         if (R > 0) seg = (int32_t)std::min<uint64_t>((uint64_t)left, R - c->sweep % R);
         if (seg > kGraphChunk) seg = kGraphChunk;
-        if (c->opt.use_graph && !ev) {
+        // one or two sweeps are cheaper launched than replayed (8192 beads, one
+        // sweep and a wait: 17 against 28 us; four: 44 against 39 us)
+        if (c->opt.use_graph && !ev && seg > 2) {
             hipGraphExec_t ex;
             if ((rc = graph_for(c, seg, &ex)) != SOMA_OK) return rc;
             HIPCHK(c, hipGraphLaunch(ex, c->stream));

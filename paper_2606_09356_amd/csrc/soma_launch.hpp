@@ -27,6 +27,8 @@ struct SweepArgs {
     int *C0, *C1, *C2;             // cells (CELL only)
     uint2 *halo;                   // stream tiles: boundary bead pairs, see halo_index
     int64_t halo_cap;              // stream tile entries per halo array
+    int one_P, one_G, one_chains;  // a context of one system, wave or block tiles: its pairs per chain, chains
+    float one_inv_P;               //   per tile and chains (the tiles follow from them); else one_P = 0
     const Tile *tiles;
     int n_tiles;
     const Tile *ptiles;            // block tiles (chains packed over the waves of a block)
@@ -35,6 +37,7 @@ struct SweepArgs {
                                    // (only with max_blocks == 0)
     int max_blocks;                // 0: one tile per wave; else the grid size (waves loop over tiles)
     int xcd_remap;
+    int n_systems, sys0_P, sys0_chains;   // the number of systems, and system 0's pairs per chain and chains
     uint32_t *base;                // two count buffers of count_words words each
     uint32_t *delta;               // three delta buffers of count_words words each
     int64_t count_words;           // uint32 words per buffer
