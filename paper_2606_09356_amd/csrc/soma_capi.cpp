@@ -856,10 +856,11 @@ soma::InitArgs init_args(const soma_ctx *c, const HostSys &h)
 {
     soma::InitArgs ia{};
     ia.repr = c->repr;
-    ia.n_chains = h.d.n_chains;
+    ia.tiles = c->d_tiles();
+    ia.tile_begin = h.tile_begin;
+    ia.tile_end = h.tile_end;
+    ia.chain_id = c->chain_id();
     ia.N = h.d.N;
-    ia.stride = 2 * h.dev.P;
-    ia.slot_off = h.dev.slot_off;
     ia.sys_id = h.dev.sys_id;
     ia.seed = c->opt.seed;
     for (int a = 0; a < 3; ++a) {
@@ -1651,7 +1652,6 @@ int soma_place_from_fields(soma_ctx *c, int32_t sys, const float *phi)
     soma::PlaceArgs pa{};
     pa.ia = init_args(c, h);
     pa.sys = c->d_sys() + sys;
-    pa.chain_id = c->chain_id();
     pa.chain_class = c->chain_class();
     pa.chain_off = h.dev.chain_off;
     pa.cell_off = h.dev.cell_off;

@@ -147,8 +147,10 @@ struct FieldArgs {
 
 struct InitArgs {
     int repr;
-    int n_chains, N, stride;
-    int64_t slot_off;
+    const Tile *tiles;             // wave tiles
+    int tile_begin, tile_end;      // of the system
+    const uint32_t *chain_id;      // logical chain id per slot of the context
+    int N;
     uint32_t sys_id;
     uint64_t seed;
     double box[3];
@@ -164,7 +166,6 @@ struct InitArgs {
 struct PlaceArgs {
     InitArgs ia;                   // representation, stream, walls, output arrays
     const DevSys *sys;             // the system's table entry
-    const uint32_t *chain_id;      // logical chain id per slot of the context
     const uint8_t *chain_class;    // per logical chain of the context
     int64_t chain_off, cell_off, n_cells;
     int grid[3];
