@@ -41,6 +41,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "soma_boxmuller.hpp"
 #include "soma_launch.hpp"
 #include "soma_types.hpp"
 
@@ -1269,16 +1270,8 @@ __global__ __launch_bounds__(256) void k_stream_halo(HaloArgs a)
 __device__ __forceinline__ void smc_draw(uint32_t bead, uint32_t chain, uint32_t sweep, uint32_t sys,
                                          uint32_t k0, uint32_t k1, double xi[3], float &u)
 {
-    const double two_pi = 6.283185307179586476925286766559;
     const uint4 w = philox4x32_10(make_uint4(bead, chain, sweep, sys), k0, k1);
-    const double u1 = ((double)(w.x >> 8) + 0.5) * 0x1p-24;
-    const double u2 = (double)(w.y >> 8) * 0x1p-24;
-    const double u3 = ((double)(w.z >> 8) + 0.5) * 0x1p-24;
-    const double u4 = (double)(w.w >> 8) * 0x1p-24;
-    const double r1 = sqrt(-2.0 * log(u1)), r2 = sqrt(-2.0 * log(u3));
-    xi[0] = r1 * cos(two_pi * u2);
-    xi[1] = r1 * sin(two_pi * u2);
-    xi[2] = r2 * cos(two_pi * u4);
+    box_muller3(w.x, w.y, w.z, w.w, xi);
     const uint4 w2 = philox4x32_10(make_uint4(bead + 256u, chain, sweep, sys), k0, k1);
     u = (float)(w2.x >> 8) * 0x1p-24f;
 }
