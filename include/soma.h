@@ -122,7 +122,8 @@ typedef struct {
     uint64_t seed;             /* Philox key */
     int32_t pos_repr;          /* SOMA_POS_* */
     int32_t count_width;       /* SOMA_COUNT_* */
-    int32_t use_graph;         /* nonzero: soma_mc_sweep replays a captured hipGraph per sweep count */
+    int32_t use_graph;         /* nonzero: soma_mc_sweep replays a captured hipGraph per sweep count
+                                  (one or two sweeps are launched directly) */
     int32_t density_mode;      /* how accepted cell changes reach the counts (merged per
                                   wave, then device atomics):
                                   0: -1/+1 on the old and new cell's words of a delta buffer,
